@@ -274,9 +274,10 @@ struct hec_tri {
     int32_t K = 0, KC = 4, ldq = 0, nparts = 0, nss = 0, W = 0, S = 0;  // KC: K padded to 4/8/16/32
     int32_t NS = 1;                          // solver wavefronts per workgroup
     int32_t D64 = 0, D32 = 0;                // ring depths for the FP64 / FP32 solve
-    bool blocked = true;                     // false: rows too long for LDS slots, per-row polling kernel
-    int32_t nchunks = 0;                     // fallback plan: 64-row chunks of one level
-    hec::DevBuf<int32_t> chunk_ptr;
+    bool blocked = true;                     // false: rows too long for LDS slots, per-row polling kernel:
+                                             // entries row by row (enc, val: row_ptr[q] .. row_ptr[q + 1])
+    int32_t nitems = 0;                      // its items: (first position, rows; 0 rows: one long row)
+    hec::DevBuf<int32_t> items, row_ptr;
     size_t lds64 = 0, lds32 = 0;             // dynamic LDS bytes of the solve kernels
     hec::DevBuf<int32_t> part_ss;   // nparts+1: sub-segment range of each part
     hec::DevBuf<int32_t> part_pos;  // nparts+1: first position of each part
@@ -287,7 +288,7 @@ struct hec_tri {
     hec::DevBuf<int32_t> other;     // lower: the row's position in the upper plan; upper with RAS: the
                                     // system row an owned stacked row is written to (-1: overlap row)
     hec::DevBuf<int32_t> bmap;      // lower with RAS: the system row whose right-hand side a position reads
-    hec::DevBuf<int32_t> enc;       // K*ldq: -(local position+1) inside the part, position outside, INT_MIN pad
+    hec::DevBuf<int32_t> enc;       // K*ldq (blocked): -(local position+1) inside the part, position outside, INT_MIN pad
     hec::DevBuf<double> val;
     hec::DevBuf<float> val32;
     hec::DevBuf<double> piv;        // upper only: u_ii per position

@@ -324,7 +324,9 @@ inline int32_t choose_tile_side(int32_t n, const std::vector<int32_t> &lev, int3
 //  * D64/D32: LDS ring depth for the FP64/FP32 solves; 0 when the plan does not
 //    fit in LDS (more than 32 entries per row): then blocked == false and the
 //    solve polls every dependency (level-order positions in 64-row chunks).
-//    flat == true asks for that level-order layout directly.
+//    flat == true asks for that level-order layout directly. long_slab == false
+//    leaves enc, src and psrc of a plan that does not fit to make_row_plan (a slab as
+//    wide as the longest row is mostly padding there).
 struct HostPlan {
     int32_t n = 0, nlev = 0, K = 0, KC = 4, ldq = 0, nparts = 0, nss = 0, W = 64, S = 0, D64 = 0, D32 = 0, NS = 1;
     bool blocked = false;
@@ -337,7 +339,7 @@ struct HostPlan {
 inline void make_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, const int32_t *diag, int32_t gnx,
                       int32_t gny, int32_t gnz, bool upper, bool has_f32, int64_t lds_max, HostPlan &P,
                       bool flat = false, const std::vector<int32_t> *blocks = nullptr, int solvers = kSolvers,
-                      int32_t tile = 0) {
+                      int32_t tile = 0, bool long_slab = true) {
     P = HostPlan();
     P.n = n;
     P.nlev = compute_levels(n, LUp, LUj, diag, upper, P.level_ptr, P.perm, &P.lev);
@@ -553,10 +555,11 @@ inline void make_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, const i
                     : lds_bytes<double, false>(P.KC, P.W, P.D64, P.S, P.NS);
     P.lds32 = upper ? lds_bytes<float, true>(P.KC, P.W, P.D32, P.S, P.NS)
                     : lds_bytes<float, false>(P.KC, P.W, P.D32, P.S, P.NS);
+    if (upper) P.psrc.assign(P.ldq, -1);
+    if (!P.blocked && !flat && !long_slab) return;  // make_row_plan lays the entries out instead
     const size_t slab = (size_t)K * P.ldq;
     P.enc.assign(slab, kPad);
     P.src.assign(slab, -1);
-    if (upper) P.psrc.assign(P.ldq, -1);
     for (int32_t q = 0; q < n; ++q) {
         int32_t i = grow[q];
         int32_t a, b;
@@ -568,6 +571,43 @@ inline void make_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, const i
                                              : flat                                   ? j
                                                                                       : pos[j];
             P.src[(size_t)s2 * P.ldq + q] = e;
+        }
+        if (upper) P.psrc[q] = diag[i];
+    }
+}
+
+// Row layout of a plan that is not blocked (made with long_slab == false): inside each
+// level the rows of more than `shortmax` entries come first, then the others, both by
+// row (P.grow, P.pos and P.psrc follow); the entries of position q are rptr[q] ..
+// rptr[q + 1] - 1 of P.enc (the dependency's position) and P.src. items: pairs (first
+// position, rows): up to `group` short rows of one level, or 0 for one long row.
+inline void make_row_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, const int32_t *diag, bool upper,
+                          int32_t shortmax, int32_t group, HostPlan &P, std::vector<int32_t> &rptr,
+                          std::vector<int32_t> &items) {
+    auto len = [&](int32_t i) { return upper ? LUp[i + 1] - diag[i] - 1 : diag[i] - LUp[i]; };
+    items.clear();
+    for (int32_t l = 0, q = 0; l < P.nlev; ++l) {
+        const int32_t a = P.level_ptr[l], b = P.level_ptr[l + 1];
+        for (int32_t t = a; t < b; ++t)
+            if (len(P.perm[t]) > shortmax) {
+                items.insert(items.end(), {q, 0});
+                P.grow[q++] = P.perm[t];
+            }
+        const int32_t q0 = q;
+        for (int32_t t = a; t < b; ++t)
+            if (len(P.perm[t]) <= shortmax) P.grow[q++] = P.perm[t];
+        for (int32_t c = q0; c < q; c += group) items.insert(items.end(), {c, std::min(group, q - c)});
+    }
+    for (int32_t q = 0; q < n; ++q) P.pos[P.grow[q]] = q;
+    rptr.assign((size_t)n + 1, 0);
+    for (int32_t q = 0; q < n; ++q) rptr[q + 1] = rptr[q] + len(P.grow[q]);
+    P.enc.resize(rptr[n]);
+    P.src.resize(rptr[n]);
+    for (int32_t q = 0; q < n; ++q) {
+        const int32_t i = P.grow[q], e0 = upper ? diag[i] + 1 : LUp[i];
+        for (int32_t t = rptr[q]; t < rptr[q + 1]; ++t) {
+            P.src[t] = e0 + (t - rptr[q]);
+            P.enc[t] = P.pos[LUj[P.src[t]]];
         }
         if (upper) P.psrc[q] = diag[i];
     }

@@ -594,91 +594,127 @@ __global__ __launch_bounds__(kBlkThreads) void k_trsv_blk(PlanArgs P, const T *_
     }
 }
 
-// Fallback for triangles whose rows are too long for the LDS slots: rows in
-// level order cut into 64-row chunks inside a level, wavefronts take chunks in
-// increasing order from a ticket counter and poll every dependency in global
-// memory (a chunk only waits for chunks taken by running wavefronts).
+// Triangles whose rows are too long for the LDS slots (more than 32 entries: ILU(3)
+// fill, irregular matrices). Rows in level order, each level's rows of more than
+// kRowShort entries first; a wavefront solves one long row or kRowGroup short ones
+// (8 lanes a row), the lanes striding the row's entries, which are stored row by row.
+// Workgroups claim kRowWaves consecutive items at a time from a ticket counter, the next
+// claim already on its way while the current items are solved, and poll every
+// dependency in global memory: an item only waits for items of earlier levels, claimed
+// before it by running workgroups, so the lowest unfinished item can always proceed.
+//
+// Bound: a level costs one device-coherent store and load between compute units (1.2 us
+// measured) plus the row's own loads, which are issued levels ahead of time because
+// 2048 wavefronts hold more rows than a level has. One row per lane over a padded slab
+// (every row walking the longest row's slots, one batch of polls after another) took
+// 5.78 ms for the L-then-U pair of a 60,000-row power-law ILU(0) (rows of 4 to 512
+// entries, 31 levels); this takes 0.15 ms.
+constexpr int kRowShort = 64;  // most entries of a row solved by a group of 8 lanes: one
+                               // or two batches of 4 per lane; longer rows take a wavefront
+constexpr int kRowGroup = 8;   // rows of a short item
+constexpr int kRowWaves = 8;   // wavefronts per workgroup, one item each per claim
+
 template <class T, bool UPPER>
-__global__ __launch_bounds__(256) void k_trsv_sf(int32_t nchunks, const int32_t *__restrict__ chunk_ptr, int32_t K,
-                                                 int32_t ldq, const int32_t *__restrict__ grow,
-                                                 const int32_t *__restrict__ other, const int32_t *__restrict__ enc,
-                                                 const T *__restrict__ val, const T *__restrict__ piv,
-                                                 SolveIO<T> io, uint32_t *sync, const int32_t *skip,
-                                                 uint32_t *err, uint32_t spin) {
+__global__ __launch_bounds__(64 * kRowWaves) void k_trsv_row(int32_t nitems, const int2 *__restrict__ items,
+                                                             const int32_t *__restrict__ ptr,
+                                                             const int32_t *__restrict__ grow,
+                                                             const int32_t *__restrict__ other,
+                                                             const int32_t *__restrict__ enc,
+                                                             const T *__restrict__ val, const T *__restrict__ piv,
+                                                             SolveIO<T> io, uint32_t *sync, const int32_t *skip,
+                                                             uint32_t *err, uint32_t spin) {
     using U = typename Sentinel<T>::U;
     constexpr U SENT = Sentinel<T>::bits;
     if (skip && *skip) return;
     fill_sentinel(io);
-    T *const xq = io.xq;
-    T *const x = io.x;
-    T *const yother = io.yother;
-    const int lane = threadIdx.x & 63;
-    for (;;) {
-        uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(&sync[0], 1u);
-        t = __shfl(t, 0);
-        if (t >= (uint32_t)nchunks) break;
-        const int32_t q = chunk_ptr[t] + lane;
-        bool quit = false;  // this lane's wait gave up (here or, through the error word, elsewhere)
-        if (q < chunk_ptr[t + 1]) {
-            const int32_t gi = grow[q];
-            T acc = io.b[io.bmap ? io.bmap[q] : io.b_by_row ? gi : q];
-            for (int32_t s0 = 0; s0 < K; s0 += kBatch) {
-                const int nb = min(kBatch, K - s0);
-                int es[kBatch];
-                T vs[kBatch];
-                U xs[kBatch];
+    // by the round's parity: its claim, and whether a wave gave up in the round before
+    __shared__ int s_claim[2], s_abort[2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // rows q0 .. q0 + cnt - 1, G lanes each; false: a wait gave up
+    auto solve = [&](auto gsz, auto bsz, int32_t q0, int32_t cnt) {
+        constexpr int G = decltype(gsz)::value, B = decltype(bsz)::value;
+        const int g = lane % G, r = lane / G;
+        const bool live = r < cnt;
+        const int32_t q = q0 + (live ? r : 0);
+        const int32_t e1 = live ? ptr[q + 1] : 0;
+        int32_t e = live ? ptr[q] + g : 0;
+        const bool lead = live && g == 0;
+        const int32_t gi = lead ? grow[q] : 0;
+        const T rhs = lead ? io.b[io.bmap ? io.bmap[q] : io.b_by_row ? gi : q] : (T)0;
+        T pv = (T)1;
+        if constexpr (UPPER) pv = lead ? piv[q] : (T)1;
+        T acc = (T)0;
+        while (__ballot(e < e1) != 0) {
+            uint32_t it = 0;
+            int es[B];
+            T vs[B];
+            U xs[B];
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    es[u] = kPad;
-                    vs[u] = (T)0;
-                    if (u < nb) {
-                        es[u] = enc[(size_t)(s0 + u) * ldq + q];
-                        vs[u] = val[(size_t)(s0 + u) * ldq + q];
-                    }
-                }
+            for (int u = 0; u < B; ++u) {
+                const bool in = e + u * G < e1;
+                es[u] = in ? enc[e + u * G] : kPad;
+                vs[u] = in ? val[e + u * G] : (T)0;
+            }
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) xs[u] = u < nb ? first_poll(xq, es[u]) : (U)0;
+            for (int u = 0; u < B; ++u) xs[u] = first_poll(io.xq, es[u]);
+            for (;;) {  // only the pending entries are reloaded
                 bool pend = false;
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) pend |= u < nb && xs[u] == SENT;
-                uint32_t it = 0;
-                while (pend) {  // only the pending entries are reloaded
-                    ++it;
-                    if (it > spin || ((it & 63) == 0 && timed_out(err))) {
-                        record_timeout(err);
-                        quit = true;
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
+                for (int u = 0; u < B; ++u) pend |= xs[u] == SENT;
+                if (__ballot(pend) == 0) break;
+                ++it;
+                if (it > spin || ((it & 63) == 0 && timed_out(err))) return false;
+                __builtin_amdgcn_s_sleep(1);
 #pragma unroll
-                    for (int u = 0; u < kBatch; ++u)
-                        if (u < nb && xs[u] == SENT) xs[u] = load_coherent(xq + es[u]);
-                    pend = false;
-#pragma unroll
-                    for (int u = 0; u < kBatch; ++u) pend |= u < nb && xs[u] == SENT;
-                }
-                if (quit) break;
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u)
-                    if (u < nb && es[u] != kPad) acc -= vs[u] * from_bits<T>(xs[u]);
+                for (int u = 0; u < B; ++u)
+                    if (xs[u] == SENT) xs[u] = load_coherent(io.xq + es[u]);
             }
-            if (!quit) {  // (after a give-up nothing more is published)
-                if constexpr (UPPER) acc = acc / piv[q];
-                store_coherent(xq + q, acc);
-                if (x) x[gi] = acc;
-                if (yother) {
-                    const int32_t o = other[q];
-                    if (o >= 0) yother[o] = acc;
-                }
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                if (es[u] != kPad) acc += vs[u] * from_bits<T>(xs[u]);
+            e += G * B;
+        }
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+        if (lead) {
+            T v = rhs - acc;
+            if constexpr (UPPER) v = v / pv;
+            store_coherent(io.xq + q, v);
+            if (io.x) io.x[gi] = v;
+            if (io.yother) {
+                const int32_t o = other[q];
+                if (o >= 0) io.yother[o] = v;
             }
         }
-        if (__ballot(quit) != 0) break;  // every lane is back here: the wave stops as a whole
+        return true;
+    };
+    if (threadIdx.x == 0) {
+        s_abort[0] = s_abort[1] = 0;
+        s_claim[0] = (int)atomicAdd(&sync[0], 1u);
     }
-    if (lane == 0) {
-        const uint32_t nwaves = gridDim.x * (blockDim.x >> 6);
-        uint32_t d = atomicAdd(&sync[1], 1u);
-        if (d == nwaves - 1) {
+    for (int round = 0;; ++round) {
+        __syncthreads();
+        const int c = s_claim[round & 1];
+        if (s_abort[round & 1] || (int64_t)c * kRowWaves >= nitems) break;  // uniform: read after the barrier
+        uint32_t next = 0;
+        if (threadIdx.x == 0) next = atomicAdd(&sync[0], 1u);
+        const int i = c * kRowWaves + wave;
+        if (i < nitems) {
+            const int2 item = items[i];
+            const int32_t q0 = __builtin_amdgcn_readfirstlane(item.x), cnt = __builtin_amdgcn_readfirstlane(item.y);
+            const bool ok = cnt > 0 ? solve(std::integral_constant<int, 64 / kRowGroup>(),
+                                            std::integral_constant<int, 4>(), q0, cnt)
+                                    : solve(std::integral_constant<int, 64>(), std::integral_constant<int, 8>(), q0, 1);
+            if (!ok) {  // nothing more is published; every wave of the workgroup leaves at the barrier
+                record_timeout(err);
+                s_abort[(round + 1) & 1] = 1;
+            }
+        }
+        if (threadIdx.x == 0) s_claim[(round + 1) & 1] = (int)next;
+    }
+    if (threadIdx.x == 0) {  // the last workgroup out resets the counters for the next launch
+        const uint32_t d = atomicAdd(&sync[1], 1u);
+        if (d == gridDim.x - 1) {
             __hip_atomic_store(&sync[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(&sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -1281,15 +1317,16 @@ void launch_blk(const hec_tri &tri, uint32_t *sync, uint32_t *err, const SolveIO
                 const int32_t *skip) {
     const uint32_t spin = spin_limit();
     T *const yother = io.yother;
-    if (tri.nparts == 0 && tri.nchunks == 0) return;
+    if (tri.nparts == 0 && tri.nitems == 0) return;
     const bool f64 = sizeof(T) == 8;
     if (!tri.blocked) {
         const T *val = f64 ? (const T *)tri.val.get() : (const T *)tri.val32.get();
         const T *piv = UPPER ? (f64 ? (const T *)tri.piv.get() : (const T *)tri.piv32.get()) : nullptr;
-        int waves = std::min(tri.nchunks, 1024);
-        k_trsv_sf<T, UPPER><<<(waves + 3) / 4, 256, 0, s>>>(tri.nchunks, tri.chunk_ptr.get(), tri.K, tri.ldq,
-                                                          tri.grow.get(), yother ? tri.other.get() : nullptr,
-                                                          tri.enc.get(), val, piv, io, sync, skip, err, spin);
+        const int grid = std::min((tri.nitems + kRowWaves - 1) / kRowWaves, 256);
+        k_trsv_row<T, UPPER><<<grid, 64 * kRowWaves, 0, s>>>(tri.nitems, (const int2 *)tri.items.get(),
+                                                             tri.row_ptr.get(), tri.grow.get(),
+                                                             yother ? tri.other.get() : nullptr, tri.enc.get(), val,
+                                                             piv, io, sync, skip, err, spin);
         HEC_CHECK_LAUNCH();
         return;
     }
@@ -1507,7 +1544,12 @@ void build_tri(const hec_ilu_s &M, bool upper, hec_tri &tri, const hec_tri *uppe
     const int32_t n = M.n;
     plan::HostPlan P;
     plan::make_plan(n, M.hLUp.data(), M.hLUj.data(), M.hdiag.data(), M.gnx, M.gny, M.gnz, upper, M.has_f32,
-                    max_lds_per_block() - 256, P, false, M.hblocks.empty() ? nullptr : &M.hblocks);
+                    max_lds_per_block() - 256, P, false, M.hblocks.empty() ? nullptr : &M.hblocks, plan::kSolvers, 0,
+                    false);
+    std::vector<int32_t> rptr, items;  // row-polling plan: entry ranges and items (first position, rows)
+    if (n > 0 && !P.blocked)
+        plan::make_row_plan(n, M.hLUp.data(), M.hLUj.data(), M.hdiag.data(), upper, kRowShort, kRowGroup, P, rptr,
+                            items);
     tri.nlev = P.nlev;
     tri.hlevel_ptr = std::move(P.level_ptr);
     tri.hperm = std::move(P.perm);
@@ -1525,9 +1567,11 @@ void build_tri(const hec_ilu_s &M, bool upper, hec_tri &tri, const hec_tri *uppe
     tri.lds64 = P.lds64;
     tri.lds32 = P.lds32;
     if (!P.blocked) {
-        tri.nchunks = (int32_t)P.chunks.size() - 1;
-        tri.chunk_ptr.alloc(P.chunks.size());
-        tri.chunk_ptr.upload(P.chunks.data(), P.chunks.size(), s);
+        tri.nitems = (int32_t)items.size() / 2;
+        tri.items.alloc(items.size());
+        tri.items.upload(items.data(), items.size(), s);
+        tri.row_ptr.alloc(rptr.size());
+        tri.row_ptr.upload(rptr.data(), rptr.size(), s);
     }
     tri.part_ss.alloc(P.part_ss.size());
     tri.part_ss.upload(P.part_ss.data(), P.part_ss.size(), s);
@@ -1569,7 +1613,7 @@ void build_tri(const hec_ilu_s &M, bool upper, hec_tri &tri, const hec_tri *uppe
         tri.other.upload(other.data(), n, s);
         HEC_HIP(hipStreamSynchronize(s));  // `other` is uploaded from host memory that ends here
     }
-    const size_t slab = (size_t)P.K * P.ldq;
+    const size_t slab = P.enc.size();  // K * ldq slots, or the entries of a row-polling plan
     tri.enc.alloc(slab);
     tri.enc.upload(P.enc.data(), slab, s);
     tri.val.alloc(slab);
