@@ -198,7 +198,7 @@ struct OpCycleStart : NoInit {
 __device__ void givens_col(int j, double hn, const double *src, double *sd, int32_t *si, int32_t *hf,
                            const GLayout &L) {
     __shared__ double col[kMaxRestart + 1];
-    __shared__ double rcs[kMaxRestart], rsn[kMaxRestart];
+    __shared__ double rcs[kMaxRestart], rsn[kMaxRestart], rot[kMaxRestart + 1];
     const int t = threadIdx.x;
     if (t <= j) col[t] = src[t];
     if (t < j) {
@@ -208,10 +208,13 @@ __device__ void givens_col(int j, double hn, const double *src, double *sd, int3
     __syncthreads();
     if (t == 0) {
         sd[SD_HNEXT] = hn;
-        double a = col[0];  // entry k of the column, rotated by rotations 0..k-1
+        // entry k of the column, rotated by rotations 0..k-1; the rotated entries go to an
+        // array of their own, so that the reads of the next ones need not wait for them
+        double a = col[0];
+#pragma unroll 8
         for (int k = 0; k < j; ++k) {
             const double c = col[k + 1], cs = rcs[k], sn = rsn[k];
-            col[k] = cs * a + sn * c;
+            rot[k] = cs * a + sn * c;
             a = -sn * a + cs * c;
         }
         const double c = hn;
@@ -223,7 +226,7 @@ __device__ void givens_col(int j, double hn, const double *src, double *sd, int3
         }
         sd[L.cs + j] = cs;
         sd[L.sn + j] = sn;
-        col[j] = cs * a + sn * c;
+        rot[j] = cs * a + sn * c;
         const double gj = sd[L.g + j];
         sd[L.g + j + 1] = -sn * gj;
         sd[L.g + j] = cs * gj;
@@ -237,7 +240,7 @@ __device__ void givens_col(int j, double hn, const double *src, double *sd, int3
         }
     }
     __syncthreads();
-    if (t <= j) sd[L.Hij(t, j)] = col[t];
+    if (t <= j) sd[L.Hij(t, j)] = rot[t];
 }
 
 // The same with the column h1 + h2 (the two Gram-Schmidt passes' coefficients).
@@ -511,51 +514,87 @@ __global__ __launch_bounds__(RB) void k_dgs_dots(int64_t n, const VT *__restrict
     }
 }
 
-// Update pass of step s (nf = s), after the dot pass's sums were finished into sd[L.ds].
-// Every workgroup first forms the step's scalars from those sums in the same order (so all
-// agree); workgroup 0 also completes column s-1 (its Givens step and convergence test) and
-// stores column s, provisional until the next step (a happy breakdown, beta = 0, completes
-// it at once). Then v_s = u' and v_{s+1} are written in one pass over the rows.
-// w == NULL: the cycle's tail (column s-1 only; no vector work).
+// Update pass of step s (nf = s), after the dot pass. Every workgroup first forms the
+// step's scalars from the dot pass's sums in the same order (so all agree); the sums come
+// from sd[L.ds] (nblocks == 0: a finishing launch put them there), or are added here from
+// the dot pass's nblocks partial sums each. Workgroup 0 does no rows: it completes column
+// s-1 (its Givens step and convergence test) and stores column s, provisional until the
+// next step (a happy breakdown, beta = 0, completes it at once). The others write v_s = u'
+// and v_{s+1} in one pass over the rows, the first rows' loads issued before the scalars
+// are formed. w == NULL: the cycle's tail (column s-1 only; one workgroup).
+// Bound: HBM at large n; at small n the latency of the scalars and of workgroup 0, which
+// run beside the rows. With the scalar sums formed by one thread and the Givens step in a
+// workgroup that also had rows, a pass over 17 to 30 vectors took
+// 24.7 us on 4,096 rows and 90 us on 2.1M; now 5.8 and 86 us.
 template <class VT, int NB>
 __global__ __launch_bounds__(RB) void k_dgs_update(int64_t n, VT *V, int64_t ldv, int nf, const VT *__restrict__ w,
-                                                   const int32_t *skip, double *sd, int32_t *si, int32_t *hf,
-                                                   GLayout L) {
+                                                   const double *__restrict__ part, int nblocks, const int32_t *skip,
+                                                   double *sd, int32_t *si, int32_t *hf, GLayout L) {
     constexpr int U = kMaxRestart / NB;
     constexpr int64_t TR = 64 * U;
     if (skip && *skip) return;
-    __shared__ double ca[NB], ct[NB], sv[4], col[kMaxRestart + 1];
-    const double *ds = sd + L.ds;
-    if (threadIdx.x == 0) {
-        double alpha = 1.0;  // v_0 = r / ||r|| is final as it stands
-        if (nf > 0) {
-            double aa = 0.0;
-            for (int k = 0; k < nf; ++k) aa += ds[k] * ds[k];
-            alpha = sqrt(fmax(ds[2 * nf] - aa, 0.0));
-            if (!(alpha > 0.0)) alpha = 1.0;  // u in the span of V_f: only after a breakdown the flags already stop
-        }
-        double h = 0.0, beta = 0.0;
-        if (w) {
-            double at = 0.0, tt = 0.0;
-            for (int k = 0; k < nf; ++k) {
-                at += ds[k] * ds[nf + k];
-                tt += ds[nf + k] * ds[nf + k];
+    __shared__ double ds[2 * NB + 4], ca[NB], ct[NB], col[kMaxRestart + 1];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    constexpr bool NT = NB == kMaxRestart || sizeof(VT) == 4;
+    VT *const u = V + (int64_t)nf * ldv;
+    VT *const vn = u + ldv;
+    const int64_t nsteps = (n + TR - 1) / TR;
+    VT vk[U][NB];
+    VT uv[U], wv[U];
+    auto load = [&](int64_t t) {
+        // no per-lane bounds checks where the whole step is inside the vectors (uniform):
+        // the loads are then one straight run, all in flight at once
+        if ((t + 1) * TR <= n) {
+#pragma unroll
+            for (int c = 0; c < U; ++c) {
+                const int64_t i = t * TR + 64 * c + lane;
+                uv[c] = load_elem<VT, NT>(u, i);
+                wv[c] = load_elem<VT, NT>(w, i);
+#pragma unroll
+                for (int k = 0; k < NB; ++k) vk[c][k] = k < nf ? load_elem<VT, NT>(V + k * ldv, i) : (VT)0;
             }
-            h = (ds[2 * nf + 1] - at) / alpha;
-            beta = sqrt(fmax(ds[2 * nf + 2] - tt - h * h, 0.0));
+        } else {
+#pragma unroll
+            for (int c = 0; c < U; ++c) {
+                const int64_t i = t * TR + 64 * c + lane;
+                const bool live = i < n;
+                uv[c] = live ? load_elem<VT, NT>(u, i) : (VT)0;
+                wv[c] = live ? load_elem<VT, NT>(w, i) : (VT)0;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) vk[c][k] = live && k < nf ? load_elem<VT, NT>(V + k * ldv, i) : (VT)0;
+            }
         }
-        sv[0] = alpha;
-        sv[1] = h;
-        sv[2] = beta;
+    };
+    int64_t t = ((int64_t)blockIdx.x - 1) * 4 + q;
+    if (blockIdx.x > 0 && t < nsteps) load(t);
+    // the sums: a_0 .. a_{nf-1}, t_0 .. t_{nf-1}, u.u, u.w, w.w
+    if ((int)threadIdx.x < 2 * nf + 3) {
+        const int k = threadIdx.x;
+        double v = 0.0;
+        if (nblocks == 0) {
+            v = sd[L.ds + k];
+        } else {
+            const double *p = part + (size_t)k * nblocks;
+#pragma unroll 8
+            for (int b = 0; b < nblocks; ++b) v += p[b];
+        }
+        ds[k] = v;
     }
     __syncthreads();
-    const double alpha = sv[0], h = sv[1], beta = sv[2];
-    const double cu = h / alpha;
-    if ((int)threadIdx.x < nf) {
-        const int k = threadIdx.x;
-        ca[k] = ds[k];
-        ct[k] = ds[nf + k] - ds[k] * cu;
+    // every wavefront forms the scalars itself (lane k: vector k)
+    const double da = lane < nf ? ds[lane] : 0.0, dt = lane < nf ? ds[nf + lane] : 0.0;
+    const double aa = wave_sum(da * da), at = wave_sum(da * dt), tt = wave_sum(dt * dt);
+    double alpha = 1.0;  // v_0 = r / ||r|| is final as it stands
+    if (nf > 0) {
+        alpha = sqrt(fmax(ds[2 * nf] - aa, 0.0));
+        if (!(alpha > 0.0)) alpha = 1.0;  // u in the span of V_f: only after a breakdown the flags already stop
     }
+    double h = 0.0, beta = 0.0;
+    if (w) {
+        h = (ds[2 * nf + 1] - at) / alpha;
+        beta = sqrt(fmax(ds[2 * nf + 2] - tt - h * h, 0.0));
+    }
+    const double cu = h / alpha;
     if (blockIdx.x == 0) {
         // column s - 1, complete now: entries += its provisional subdiagonal times a
         if (nf > 0) {
@@ -579,28 +618,18 @@ __global__ __launch_bounds__(RB) void k_dgs_update(int64_t n, VT *V, int64_t ldv
                 givens_col(nf, 0.0, col, sd, si, hf, L);
             }
         }
+        return;
+    }
+    if (q == 0 && lane < nf) {
+        ca[lane] = da;
+        ct[lane] = dt - da * cu;
     }
     __syncthreads();
-    if (!w) return;
     const double bdiv = beta > 0.0 ? beta : 1.0;
-    VT *const u = V + (int64_t)nf * ldv;
-    VT *const vn = u + ldv;
-    constexpr bool NT = NB == kMaxRestart || sizeof(VT) == 4;
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int64_t nsteps = (n + TR - 1) / TR;
-    for (int64_t t = (int64_t)blockIdx.x * 4 + q; t < nsteps; t += (int64_t)gridDim.x * 4) {
-        VT vk[U][NB];
-        VT uv[U], wv[U];
-        const bool inside = (t + 1) * TR <= n;
-#pragma unroll
-        for (int c = 0; c < U; ++c) {
-            const int64_t i = t * TR + 64 * c + lane;
-            const bool live = inside || i < n;
-            uv[c] = live ? load_elem<VT, NT>(u, i) : (VT)0;
-            wv[c] = live ? load_elem<VT, NT>(w, i) : (VT)0;
-#pragma unroll
-            for (int k = 0; k < NB; ++k) vk[c][k] = live && k < nf ? load_elem<VT, NT>(V + k * ldv, i) : (VT)0;
-        }
+    while (t < nsteps) {
+        // the coefficients are read from LDS in every step: held in registers (128 of them
+        // at NB = 32) they halve the wavefronts in flight, 173 against 86 us a pass
+        __asm__ volatile("" ::: "memory");
 #pragma unroll
         for (int c = 0; c < U; ++c) {
             double sa = 0.0, st = 0.0;
@@ -617,19 +646,40 @@ __global__ __launch_bounds__(RB) void k_dgs_update(int64_t n, VT *V, int64_t ldv
                 vn[i] = (VT)(((double)wv[c] - st - ud * cu) / bdiv);
             }
         }
+        t += ((int64_t)gridDim.x - 1) * 4;
+        if (t < nsteps) load(t);
     }
 }
 
+// Workgroups of a dot pass at vector bound NB: one step of 64 * 32 / NB rows per
+// wavefront until the grid is full.
+template <int NB>
+inline unsigned dgs_blocks(int64_t n) {
+    const int64_t rows = 4 * 64 * (kMaxRestart / NB);
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + rows - 1) / rows, kMaxRedBlocks));
+}
+
+// Up to this many workgroups the update pass adds the dot pass's partial sums itself
+// (at most 32 x 67 values per workgroup, one round of loads), which saves the finishing
+// launch (4.5 us); beyond it every workgroup of the update would read more than 17 KB
+// before its rows.
+constexpr unsigned kDgsFoldBlocks = 32;
+
 template <class VT>
-void launch_dgs(unsigned gd, unsigned gu, int64_t n, VT *V, int64_t ldv, int nf, const VT *w, double *part,
-                const int32_t *skip, double *sd, int32_t *si, int32_t *hf, const GLayout &L, hipStream_t s) {
+void launch_dgs(int64_t n, VT *V, int64_t ldv, int nf, const VT *w, double *part, const int32_t *skip, double *sd,
+                int32_t *si, int32_t *hf, const GLayout &L, hipStream_t s) {
     auto go = [&](auto nb) {
         constexpr int NB = decltype(nb)::value;
+        const unsigned gd = dgs_blocks<NB>(n);
         k_dgs_dots<VT, NB><<<gd, RB, 0, s>>>(n, V, ldv, nf, w, part, skip);
         HEC_CHECK_LAUNCH();
-        k_cgs_finish<<<2 * nf + 3, RB, 0, s>>>(part, gd, sd + L.ds, skip);
-        HEC_CHECK_LAUNCH();
-        k_dgs_update<VT, NB><<<w ? gu : 1u, RB, 0, s>>>(n, V, ldv, nf, w, skip, sd, si, hf, L);
+        const bool fold = gd <= kDgsFoldBlocks;
+        if (!fold) {
+            k_cgs_finish<<<2 * nf + 3, RB, 0, s>>>(part, gd, sd + L.ds, skip);
+            HEC_CHECK_LAUNCH();
+        }
+        k_dgs_update<VT, NB><<<w ? gd + 1 : 1u, RB, 0, s>>>(n, V, ldv, nf, w, part, fold ? (int)gd : 0, skip, sd, si,
+                                                            hf, L);
         HEC_CHECK_LAUNCH();
     };
     if (nf <= 4)
@@ -1052,7 +1102,7 @@ static KrylovWS &get_ws(hec_matrix_s &A, int m, bool mixed, bool bicg, hipStream
     GLayout L(std::max(mm, 1));
     nw->sd.alloc(std::max(L.total, SD_SCALARS + 8));
     nw->si.alloc(SI_COUNT);
-    nw->part.alloc((size_t)nw->nred * kDSums);
+    nw->part.alloc((size_t)std::max<unsigned>(nw->nred, dgs_blocks<kMaxRestart>(A.n)) * kDSums);
     HEC_HIP(hipMemsetAsync(nw->si.get(), 0, SI_COUNT * sizeof(int32_t), s));
     nw->hflags = take_flags();
     nw->hsd = (double *)((char *)nw->hflags + kScalarsOffset);
@@ -1105,8 +1155,6 @@ static int gmres_cycle(hec_matrix_s &A, hec_levels_s &lv, KrylovWS &ws, int mcyc
     // (the device's done flag) and the cycle adds no columns to x
     if constexpr (sizeof(VT) == 8) {
         // FP64 basis: delayed reorthogonalisation, two passes over the basis per step
-        const unsigned gd = ws.nred;
-        const unsigned gu = (unsigned)std::min<int64_t>(ceil_div(n, (int64_t)RB * 8), kMaxRedBlocks);
         for (int j = 0; j <= mcyc; ++j) {
             // look two iterations behind, every other iteration: stop issuing work once the
             // device is done. An event record costs the stream about 6 us (it waits for the
@@ -1123,7 +1171,7 @@ static int gmres_cycle(hec_matrix_s &A, hec_levels_s &lv, KrylovWS &ws, int mcyc
                 trsv_launch<VT>(lv, HEC_LU, vj, zj, s, done);
                 spmv_launch<VT, VT, VT>(A, 1.0, zj, 0.0, w, w, s, done);
             }
-            launch_dgs<VT>(gd, gu, n, V, ldv, j, tail ? nullptr : w, ws.part.get(), done, sd, si, ws.dflags, L, s);
+            launch_dgs<VT>(n, V, ldv, j, tail ? nullptr : w, ws.part.get(), done, sd, si, ws.dflags, L, s);
             if ((j & 1) && ws.hflags) HEC_HIP(hipEventRecord(ws.ev[j + 1], s));
         }
     } else {
@@ -1301,7 +1349,7 @@ static void gmres_run(hec_matrix_s &A, hec_levels_s &lv, KrylovWS &ws, const dou
 // comes from hipGetSymbolAddress on the first call made with that device current.
 constexpr int64_t kNoAllocLdv = HEC_NOALLOC_MAX_N + HEC_BASIS_PAD;  // widest basis vector (n rounded to 64)
 constexpr int64_t kNoAllocSd = 2048;                                // scalars + Hessenberg (GLayout(32) needs 1265)
-constexpr int64_t kNoAllocPart = 4096;                              // partial sums: nred * 68 (32 * 68 at most)
+constexpr int64_t kNoAllocPart = 64 * kDSums;                       // partial sums of a dot pass's workgroups
 constexpr int64_t kNoAllocSi = 64;                                  // SI_COUNT int32 flags, in doubles
 constexpr int64_t kNoAllocDoubles = (2 * kMaxRestart + 3) * kNoAllocLdv + kNoAllocSd + kNoAllocPart + kNoAllocSi;
 static_assert(HEC_NOALLOC_MAX_N % 64 == 0, "the no-allocation bound keeps basis vectors 64-aligned");
@@ -1339,7 +1387,8 @@ static void noalloc_workspace(KrylovWS &ws, int64_t n, int m, hipStream_t s) {
     ws.m = m;
     ws.nred = red_blocks(n);
     const int64_t ldv = ws.ldv;
-    if (GLayout(m).total > kNoAllocSd || (int64_t)ws.nred * kDSums > kNoAllocPart || ldv > kNoAllocLdv)
+    if (GLayout(m).total > kNoAllocSd ||
+        (int64_t)std::max<unsigned>(ws.nred, dgs_blocks<kMaxRestart>(n)) * kDSums > kNoAllocPart || ldv > kNoAllocLdv)
         fail(HEC_ERR_INVALID_ARG, "system too large for the no-allocation scratch");
     double *q = base;
     ws.V.borrow(q, (size_t)(m + 1) * ldv);
