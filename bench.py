@@ -303,7 +303,7 @@ def main():
     trsv_share = t_trsv_lu * it_per_solve / (ms_per_step / 1e3)
 
     grid = hec.levels_grid(lv)  # the wavefront kernel (7-point ILU(0) on a grid) or the level-blocked one
-    kname = ("k_trsv_grid<double,false,8> + k_trsv_grid<double,true,8>" if grid else
+    kname = ("k_trsv_grid<double,false> + k_trsv_grid<double,true>" if grid else
              "k_trsv_blk<double,false,4> + k_trsv_blk<double,true,4>")
     roof = {"kernel": kname + " (one preconditioner solve: the lower and the upper launch)",
             "bound": "hbm", "achieved": round(trsv_gbs, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",

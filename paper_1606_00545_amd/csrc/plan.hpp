@@ -638,6 +638,8 @@ constexpr int kGT2 = 64;                     // tile side along a on a 2D grid (
 constexpr int kGT2Min = 16;                  // a 2D grid needs this many columns along a
 constexpr int kGridCoefLower = 3;            // per lane and step: back (c), below (b), left (a)
 constexpr int kGridCoefUpper = 4;            // ... and the reciprocal pivot
+constexpr int kGrid2CoefLower = 2;           // packed for a 2D grid, which has no "below": back, left
+constexpr int kGrid2CoefUpper = 3;
 
 struct GridPlan {
     int32_t NA = 0, NB = 0, NC = 0;  // extents along a, b and c

@@ -722,9 +722,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_trsv_row(int32_t nitems, con
 }
 
 // ---------------------------------------------------------------------------
-// Wavefront solve of a grid triangle (plan.hpp's GridPlan): one tile of TA x TB
-// columns per workgroup (8 x 8 on a 3D grid, which the description below follows;
-// 64 x 1 on a 2D grid), tiles claimed in order from a ticket counter (a tile only
+// Wavefront solve of a triangle on a 3D grid (plan.hpp's GridPlan): one tile of 8 x 8
+// columns per workgroup, tiles claimed in order from a ticket counter (a tile only
 // waits for tiles claimed before it, held by running workgroups).
 //  * Wavefront 0 solves. At step s lane (ma, mb) solves the row at c-index
 //    s - ma - mb of its column; that row's dependencies were solved at step s - 1:
@@ -751,8 +750,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_trsv_row(int32_t nitems, con
 //    leading steps that have all of theirs. (Several pollers would poll the same
 //    window independently; a wider window or more pollers send more device-coherent
 //    loads, and a poll takes longer the more lines it reads: at 128^3 every wider
-//    window or second poller measured slower.) A 2D tile's poller polls its one
-//    face value per step, 32 steps at a time.
+//    window or second poller measured slower.)
 //  * The other wavefronts load the coefficients (packed by claim, step and lane, so
 //    every load is a whole line) and the right-hand side of runs of steps into a
 //    ring of LDS slots. They depend on nothing but the ring, so they run ahead.
@@ -805,28 +803,23 @@ struct GridIO {
 };
 
 // Dynamic LDS of k_trsv_grid: control words, slots [ring][NCOEF + 1][64], grids
-// [ring][TB + 1][TA + 1][2] (a cell: the value from the left, the value from below).
+// [ring][9][9][2] (a cell: the value from the left, the value from below).
 constexpr size_t kGridCtrl = 256;
-template <class T, bool UPPER, int TA>
+template <class T, bool UPPER>
 constexpr size_t grid_lds_bytes() {
     constexpr int NCOEF = UPPER ? plan::kGridCoefUpper : plan::kGridCoefLower;
     return kGridCtrl + (size_t)kGridRing * (NCOEF + 1) * 64 * sizeof(T) +
-           (size_t)kGridRing * (TA + 1) * (64 / TA + 1) * 2 * sizeof(T);
+           (size_t)kGridRing * (plan::kGT + 1) * (plan::kGT + 1) * 2 * sizeof(T);
 }
 
-// TA: tile side along a (8: 8 x 8 tiles of a 3D grid; 64: 64 x 1 tiles of a 2D grid,
-// whose b-face is empty: its cells are zeroed once per tile and never written again).
-template <class T, bool UPPER, int TA>
+template <class T, bool UPPER>
 __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const T *__restrict__ coef, GridIO<T> io,
                                                                uint32_t *sync, const int32_t *skip) {
     using U = typename Sentinel<T>::U;
     constexpr U SENT = Sentinel<T>::bits;
     constexpr int NCOEF = UPPER ? plan::kGridCoefUpper : plan::kGridCoefLower;
-    static_assert(TA == plan::kGT || TA == plan::kGT2, "tile shape");
-    constexpr int TB = 64 / TA, GG = TA + 1, GA = (TA + 1) * (TB + 1) * 2, RM = kGridRing - 1;
-    // face entries per step in the face buffer: 8 and 8 on a 3D grid, the one a-face entry
-    // on a 2D grid (no tile has a tile above it there)
-    constexpr int FS = TA == TB ? TA : TB;
+    constexpr int TA = plan::kGT, TB = plan::kGT, GG = TA + 1, GA = GG * GG * 2, RM = kGridRing - 1;
+    constexpr int FS = TA;  // face entries per step in each face's buffer
     constexpr int SLOT = (NCOEF + 1) * 64;  // elements of a slot: [NCOEF][64] coefficients, [64] rhs
     if (skip && *skip) return;  // uniform: no workgroup touches the counters
     if (io.fill) {
@@ -882,8 +875,7 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const
             *s_faces = 0;
         }
         if (threadIdx.x < kGridRing) filled[threadIdx.x] = -1;
-        // step 0: no previous results (a 2D tile: every grid, whose b-face cells stay zero)
-        for (int t = threadIdx.x; t < (TB == 1 ? kGridRing * GA : GA); t += blockDim.x) xg[t] = (T)0;
+        for (int t = threadIdx.x; t < GA; t += blockDim.x) xg[t] = (T)0;  // step 0: no previous results
         __syncthreads();
         const int c = *s_claim;
         if (c >= G.nclaims) break;
@@ -906,7 +898,7 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const
             // this lane's face store (if any): a-face by mb (the corner too), b-face by ma
             const bool fst = ma == TA - 1 || (mb == TB - 1 && has_u);
             T *const fp = io.face + ((int64_t)c * 2 + (ma == TA - 1 ? 0 : 1)) * G.S * 8 +
-                          (ma == TA - 1 ? mb - (TA - 1) * FS : ma - (TB - 1) * FS);  // + FS s: the entry of step s
+                          (ma == TA - 1 ? mb : ma) - (TA - 1) * FS;  // + FS s: the entry of step s
             T xp = (T)0;  // this lane's result of the previous step (0: none)
             int ready = 0, fready = 0;
             bool bail = false;
@@ -1095,47 +1087,6 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const
                 }
             }
             __builtin_amdgcn_s_setprio(0);
-        } else if (TB == 1 && wave <= kGridPollers) {
-            // ---------------- face poller of a 2D tile: its one face value per step (the left
-            // value of lane 0), from the tile before along a. Lane l < 32 polls step w + l; a
-            // value goes into its step's grid once, when it has arrived and the solver is done
-            // with the grid's previous use; the window moves on by the leading steps that have
-            // their value, whose count is published.
-            if (wave == 1) {
-                const bool has = mta > 0;
-                const T *const fsrc = has ? io.face + (int64_t)(c - 1) * 2 * G.S * 8 : io.face;
-                int w = 0, pub = 0;
-                bool wr = false;  // this lane's value of step w + lane is in its grid
-                uint32_t it = 0;
-                while (pub < G.S) {
-                    const int dn = lds_load(s_done);
-                    const int st = w + lane;
-                    const bool can = lane < 32 && !wr && st < G.S && st < dn + kGridRing;
-                    const bool need = can && has && st < G.NC;
-                    const U v = need ? load_coherent(fsrc + st) : (U)0;
-                    if (can && (!need || v != SENT)) {
-                        xg[(st & RM) * GA] = need ? from_bits<T>(v) : (T)0;
-                        wr = true;
-                    }
-                    const uint64_t m = __ballot(wr || (lane < 32 && st >= G.S)) & 0xFFFFFFFFull;
-                    const int k = __builtin_ctzll(~m);  // leading steps of the window with their value
-                    if (w + k > pub) {
-                        pub = min(w + k, G.S);
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // after this wave's writes
-                        if (lane == 0) __hip_atomic_store(s_faces, pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        it = 0;
-                    } else {
-                        if (spun_out(it, true)) break;
-                        __builtin_amdgcn_s_sleep(HEC_GRID_POLL_SLEEP);
-                    }
-                    if (k > 0) {  // lane l takes over lane l + k's step
-                        const int from = lane + k;
-                        const int nw = __shfl((int)wr, from < 64 ? from : lane);
-                        wr = from < 32 && nw != 0;
-                        w += k;
-                    }
-                }
-            }
         } else if (wave <= kGridPollers) {
             // ---------------- face pollers: a window of 4R steps from w, step w + q + 4r in
             // lane 16q + i for r < R; i < 8: a-face entry i (lane (0, i)), i >= 8:
@@ -1270,15 +1221,418 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const
     }
 }
 
-// Packed coefficients of a wavefront plan: out[q] = value map[q] of the factor (0
-// where map[q] < 0); slot k = 3 of each step holds the reciprocal of the pivot.
+// ---------------------------------------------------------------------------
+// Wavefront solve of a triangle on a 2D grid: tiles of 64 columns side by side (64 x 1
+// GridPlan), one wavefront solving a tile: at step s lane l solves the row at c-index
+// s - l of its column. Its two dependencies were solved at step s - 1, by the lane itself
+// (a register) and by lane l - 1, whose value one DPP shift over the wavefront brings in;
+// lane 0 keeps the shift's old operand, the face value from the tile before.
+//
+// Bound: the chain of steps, one wavefront's instruction issue: two fused multiply-adds,
+// two DPP moves, four LDS accesses. So everything else is kept off the solver:
+//  * loaders stream the coefficients and the right-hand side into a ring of 64 LDS slots,
+//    8 steps each in flight per wavefront;
+//  * a poller brings in the face values, 32 steps at a time;
+//  * the solver puts each result in the place of the right-hand side it came from, and two
+//    writers take the results from there to the face buffer (device-coherent) and to the
+//    output; a slot is loaded again once its result was read.
+// Blocks of 8 steps: a block starts when its slots are loaded and its face values are in;
+// the next block's slots are read into registers while it computes if they are loaded
+// already. Lanes without a row at a step have zero coefficients and a zero right-hand
+// side: they compute zeros (or, once a solution holds infinities, NaN) that reach no row.
+// With the neighbours' values passed through LDS cells and all stores in the solver a step
+// took 132 ns; here 45 (54 with the streams of a long chain beside it; 701 x 653 L-then-U
+// pair 473 -> 215 us, 64 x 64 54 -> 28 us).
+constexpr int kG2Waves = 8, kG2Ring = 64, kG2Batch = 8, kG2Writers = 2;
+constexpr int kG2Loaders = kG2Waves - 2 - kG2Writers;  // after the solver, the poller and the writers
+constexpr int kG2Row = 68;  // elements of a step in the ring of right-hand sides: 4 more than the lanes, so
+                            // that 8 steps x 8 columns read or written at once fall on different banks
+constexpr size_t kG2Ctrl = 512;
+static_assert(plan::kGT2 == 64, "one lane per column of a tile");
+
+template <class T, bool UPPER>
+constexpr size_t grid2_lds_bytes() {
+    constexpr int NC2 = UPPER ? plan::kGrid2CoefUpper : plan::kGrid2CoefLower;
+    return kG2Ctrl + (size_t)kG2Ring * sizeof(T) + (size_t)kG2Ring * (NC2 * 64 + kG2Row) * sizeof(T);
+}
+
+// The coefficients back and left of a row, loaded and stored together (16 bytes in FP64:
+// 64 lanes read them from LDS in 10 cycles, two 8-byte reads in one ds_read2st64 in 18).
 template <class T>
-__global__ __launch_bounds__(256) void k_grid_coef(size_t n, int ncoef, const int32_t *__restrict__ map,
+struct alignas(2 * sizeof(T)) Pair {
+    T back, left;
+};
+
+// v of the lane before, lane 0: `first`.
+template <class T>
+__device__ __forceinline__ T shift_lane(T first, T v) {
+    constexpr int kWaveShr1 = 0x138;  // DPP wave_shr:1
+    if constexpr (sizeof(T) == 8) {
+        int f[2], x[2];
+        __builtin_memcpy(f, &first, 8);
+        __builtin_memcpy(x, &v, 8);
+        x[0] = __builtin_amdgcn_update_dpp(f[0], x[0], kWaveShr1, 0xF, 0xF, false);
+        x[1] = __builtin_amdgcn_update_dpp(f[1], x[1], kWaveShr1, 0xF, 0xF, false);
+        __builtin_memcpy(&v, x, 8);
+    } else {
+        int f, x;
+        __builtin_memcpy(&f, &first, 4);
+        __builtin_memcpy(&x, &v, 4);
+        x = __builtin_amdgcn_update_dpp(f, x, kWaveShr1, 0xF, 0xF, false);
+        __builtin_memcpy(&v, &x, 4);
+    }
+    return v;
+}
+
+// Lane 0: v of lane u of its 16 (other lanes: unspecified). u is a compile-time constant.
+template <int u, class T>
+__device__ __forceinline__ T lane_to_first(T v) {
+    if constexpr (u == 0) return v;
+    constexpr int kRowShl = 0x100 + u;  // DPP row_shl:u
+    int x[sizeof(T) / 4];
+    __builtin_memcpy(x, &v, sizeof(T));
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) x[k] = __builtin_amdgcn_update_dpp(0, x[k], kRowShl, 0xF, 0xF, true);
+    __builtin_memcpy(&v, x, sizeof(T));
+    return v;
+}
+
+template <class T, bool UPPER>
+__global__ __launch_bounds__(64 * kG2Waves) void k_trsv_grid2(GridArgs G, const T *__restrict__ coef, GridIO<T> io,
+                                                              uint32_t *sync, const int32_t *skip) {
+    using U = typename Sentinel<T>::U;
+    constexpr U SENT = Sentinel<T>::bits;
+    constexpr int NC2 = UPPER ? plan::kGrid2CoefUpper : plan::kGrid2CoefLower;  // back, left (and reciprocal pivot)
+    constexpr int RM = kG2Ring - 1;
+    if (skip && *skip) return;  // uniform: no workgroup touches the counters
+    if (io.fill) {
+        const T sv = from_bits<T>(SENT);
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < io.nfill;
+             i += (int64_t)gridDim.x * blockDim.x)
+            io.fill[i] = sv;
+    }
+    extern __shared__ __align__(16) char gsm[];
+    int *const filled = (int *)gsm;        // [ring]: step whose coefficients and rhs a slot holds
+    int *const s_done = filled + kG2Ring;  // steps the solver has finished
+    int *const s_faces = s_done + 1;       // leading steps whose face value is in the ring
+    int *const s_claim = s_done + 2;
+    int *const s_abort = s_done + 3;
+    int *const s_prog = s_done + 4;        // [writers]: all blocks of a writer below this step are read
+    T *const fring = (T *)(gsm + kG2Ctrl);               // [ring] face values
+    Pair<T> *const cpr = (Pair<T> *)(fring + kG2Ring);   // [ring][64] coefficients
+    T *const rhs = (T *)(cpr + kG2Ring * 64);            // [ring][kG2Row] right-hand side, then result
+    T *const rpv = rhs + kG2Ring * kG2Row;               // [ring][64] reciprocal pivot (upper)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) *s_abort = 0;
+    auto lds_load = [](const int *p) {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
+    auto lds_publish = [&](int *p, int v) {  // after this wavefront's LDS accesses above it (they complete in order)
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        if (lane == 0) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // one more poll of a wait (wave-uniform callers): true when the wait must stop
+    auto spun_out = [&](uint32_t &it, bool device_wide) {
+        ++it;
+        bool stop = it > G.spin;
+        if (!stop && (it & 63) == 0) stop = lds_load(s_abort) != 0 || (device_wide && timed_out(G.err));
+        stop = __builtin_amdgcn_readfirstlane((int)stop) != 0;
+        if (stop) {
+            __hip_atomic_store(s_abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            record_timeout(G.err);
+        }
+        return stop;
+    };
+    const int S8 = (G.S + 7) / 8 * 8;  // whole blocks: the steps past S hold no row
+    for (;;) {
+        __syncthreads();
+        if (*s_abort) break;  // uniform: read by every thread after the barrier
+        if (threadIdx.x == 0) {
+            *s_claim = (int)atomicAdd(&sync[0], 1u);
+            *s_done = 0;
+            *s_faces = 0;
+        }
+        if (threadIdx.x < kG2Ring) filled[threadIdx.x] = -1;
+        if ((int)threadIdx.x < kG2Writers) s_prog[threadIdx.x] = 0;
+        if (threadIdx.x < kG2Ring) fring[threadIdx.x] = (T)0;  // (a tile without one before it: no poller writes)
+        __syncthreads();
+        const int c = *s_claim;
+        if (c >= G.nclaims) break;
+        const int32_t ta = UPPER ? G.PA - 1 - c : c;
+        // row of column l of the tile at its c-index mc, -1: none
+        auto row_of = [&](int l, int32_t mc) -> int64_t {
+            const int32_t ga = ta * 64 + (UPPER ? 63 - l : l);
+            return ga < G.NA && (uint32_t)mc < (uint32_t)G.NC ? ga * G.sa + (UPPER ? G.NC - 1 - mc : mc) * G.sc : -1;
+        };
+        // Vectors by row are read and written 8 steps at a time, so that a wavefront's access
+        // falls on few cache lines (a step alone has 64 rows on 64 lines: 50 us more on the
+        // 701 x 653 pair): access i of 8 takes, with columns running along the unit stride,
+        // 8 steps of the 8 columns from 8 i (8 rows in a row of memory each), else, with
+        // neighbouring columns adjacent in memory, a column per lane at step (lane + i) mod 8
+        // (lanes in a row of memory at the same c-index).
+        const bool along = G.sc == 1;
+        auto acc_col = [&](int i) { return along ? 8 * i + (lane >> 3) : lane; };
+        auto acc_step = [&](int i) { return along ? lane & 7 : (lane + i) & 7; };
+        // this lane's padded tile-step position at step 0, and its change per step
+        const int64_t pq = (int64_t)c * G.S * 64 + lane;
+        const int64_t p0 = UPPER ? (int64_t)G.nclaims * G.S * 64 - 1 - pq : pq, pd = UPPER ? -64 : 64;
+        const bool has_face = c > 0, has_next = c + 1 < G.nclaims;
+
+        if (wave == 0) {
+            // ---------------- solver
+            __builtin_amdgcn_s_setprio(3);
+            struct Blk {  // a block's inputs
+                Pair<T> cv[8];
+                T bv[8], pv[8], fv;  // fv: lane u holds step u's face value
+            };
+            int ready = 0, fready = has_face ? 0 : INT_MAX;  // steps known to be loaded / to have their face value
+            bool bail = false;
+            auto ensure = [&](int s0) {  // block s0 loaded and its faces in
+                uint32_t it = 0;
+                while (ready < s0 + 8 && !bail) {  // 8 flags, one per lane, in one LDS round trip
+                    const int want = s0 + (lane & 7);
+                    const int f = __hip_atomic_load(&filled[want & RM], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (__ballot(f != want) == 0)
+                        ready = s0 + 8;
+                    else if (spun_out(it, false))
+                        bail = true;
+                }
+                it = 0;
+                while (fready < s0 + 8 && !bail) {
+                    fready = lds_load(s_faces);
+                    if (fready < s0 + 8 && spun_out(it, false)) bail = true;
+                }
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            };
+            auto load = [&](int s0, Blk &H) {
+                const int o = (s0 & RM) * 64 + lane;
+                const T *const b = rhs + (s0 & RM) * kG2Row + lane;
+                H.fv = fring[(s0 & RM) + (lane & 7)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    H.cv[u] = cpr[o + u * 64];
+                    H.bv[u] = b[u * kG2Row];
+                    H.pv[u] = (T)1;
+                    if constexpr (UPPER) H.pv[u] = rpv[o + u * 64];
+                }
+            };
+            // the block's inputs have arrived (said to the compiler, which otherwise waits for
+            // the next block's reads as well before the first step of this one)
+            auto arrived = [&](Blk &H) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    __asm__ volatile("" : "+v"(H.cv[u].back), "+v"(H.cv[u].left), "+v"(H.bv[u]));
+                    if constexpr (UPPER) __asm__ volatile("" : "+v"(H.pv[u]));
+                }
+                __asm__ volatile("" : "+v"(H.fv));
+            };
+            T xp = (T)0;  // this lane's result of the previous step (0: none)
+            // the steps of block s0, whose inputs are in cur; those of the next one are read
+            // into nxt meanwhile, and again once they are there if they were not yet
+            auto block = [&](int s0, Blk &cur, Blk &nxt) {
+                const int s1 = s0 + 8;
+                const bool pre = ready >= s1 + 8 && fready >= s1 + 8;
+                // the flags of the 16 steps from the next block: read now, looked at below
+                const int want = s1 + (lane & 15);
+                const int fl = __hip_atomic_load(&filled[want & RM], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                const int ff = __hip_atomic_load(s_faces, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                load(s1, nxt);
+                T *const o = rhs + (s0 & RM) * kG2Row + lane;
+                auto step = [&](auto uc) {
+                    constexpr int u = decltype(uc)::value;
+                    const T left = shift_lane<T>(lane_to_first<u>(cur.fv), xp);
+                    T acc;
+                    if constexpr (!UPPER) {
+                        acc = cur.bv[u] - cur.cv[u].back * xp;
+                        acc -= cur.cv[u].left * left;
+                    } else {
+                        acc = cur.bv[u] - cur.cv[u].left * left;
+                        acc -= cur.cv[u].back * xp;
+                        acc *= cur.pv[u];
+                    }
+                    o[u * kG2Row] = acc;
+                    xp = acc;
+                };
+                step(std::integral_constant<int, 0>());
+                step(std::integral_constant<int, 1>());
+                step(std::integral_constant<int, 2>());
+                step(std::integral_constant<int, 3>());
+                step(std::integral_constant<int, 4>());
+                step(std::integral_constant<int, 5>());
+                step(std::integral_constant<int, 6>());
+                step(std::integral_constant<int, 7>());
+                lds_publish(s_done, s1);
+                const uint32_t out = (uint32_t)__ballot(fl != want) & 0xFFFFu;  // steps not loaded yet
+                if ((out & 0xFFu) == 0) ready = max(ready, s1 + (out == 0 ? 16 : 8));
+                if (has_face) fready = max(fready, __builtin_amdgcn_readfirstlane(ff));
+                if (!pre && s1 < S8) {
+                    ensure(s1);
+                    load(s1, nxt);  // (after a give-up: in range, never published)
+                }
+                arrived(nxt);
+            };
+            Blk h0, h1;
+            ensure(0);
+            load(0, h0);
+            arrived(h0);
+            for (int s0 = 0; s0 < S8 && !bail; s0 += 16) {
+                block(s0, h0, h1);
+                if (s0 + 8 < S8 && !bail) block(s0 + 8, h1, h0);
+            }
+            __builtin_amdgcn_s_setprio(0);
+        } else if (wave == 1) {
+            // ---------------- face poller: lane l < 32 polls step w + l; a value goes into the ring
+            // once, when it has arrived and the solver is done with the entry's previous use;
+            // the window moves on by the leading steps that have their value
+            if (has_face) {
+                const T *const fsrc = io.face + (int64_t)(c - 1) * G.S;
+                int w = 0;
+                bool wr = false;  // this lane's value of step w + lane is in the ring
+                uint32_t it = 0;
+                while (w < S8) {
+                    const int dn = lds_load(s_done);
+                    const int st = w + lane;
+                    const bool can = lane < 32 && !wr && st < S8 && st < dn + kG2Ring;
+                    const bool need = can && st < G.NC;
+                    const U v = need ? load_coherent(fsrc + st) : (U)0;
+                    if (can && (!need || v != SENT)) {
+                        fring[st & RM] = need ? from_bits<T>(v) : (T)0;
+                        wr = true;
+                    }
+                    const uint64_t m = __ballot(wr || (lane < 32 && st >= S8)) & 0xFFFFFFFFull;
+                    const int k = __builtin_ctzll(~m);  // leading steps of the window with their value
+                    if (k == 0) {
+                        if (spun_out(it, true)) break;
+                        __builtin_amdgcn_s_sleep(1);
+                        continue;
+                    }
+                    it = 0;
+                    lds_publish(s_faces, min(w + k, S8));
+                    const int from = lane + k;  // lane l takes over lane l + k's step
+                    const int nw = __shfl((int)wr, from < 64 ? from : lane);
+                    wr = from < 32 && nw != 0;
+                    w += k;
+                }
+            }
+        } else if (wave < 2 + kG2Writers) {
+            // ---------------- writers: blocks of 8 steps in turn; the results of lane 63, which the
+            // tile after this one waits for, first
+            const int wi = wave - 2;
+            T *const fdst = io.face + (int64_t)c * G.S;
+            for (int s0 = 8 * wi; s0 < S8; s0 += 8 * kG2Writers) {
+                uint32_t it = 0;
+                bool quit = false;
+                while (lds_load(s_done) < s0 + 8) {
+                    if (spun_out(it, false)) {
+                        quit = true;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                if (quit) break;
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                const T *const p = rhs + (s0 & RM) * kG2Row;
+                if (has_next) {
+                    const int mc = s0 + lane - 63;
+                    if (lane < 8 && (uint32_t)mc < (uint32_t)G.NC)
+                        store_coherent(fdst + mc, p[lane * kG2Row + 63]);
+                }
+                T v[8];
+                if (io.xpad) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = p[u * kG2Row + lane];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (row_of(lane, s0 + u - lane) >= 0) io.x[p0 + (s0 + u) * pd] = v[u];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = p[acc_step(i) * kG2Row + acc_col(i)];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int64_t row = row_of(acc_col(i), s0 + acc_step(i) - acc_col(i));
+                        if (row >= 0) io.x[row] = v[i];
+                    }
+                }
+                lds_publish(s_prog + wi, s0 + 8 * kG2Writers);
+            }
+            lds_publish(s_prog + wi, INT_MAX);
+        } else {
+            // ---------------- loaders: runs of kG2Batch consecutive steps in turn, each run in
+            // flight at once; a run waits until its slots' previous results were read
+            constexpr int B = kG2Batch;
+            static_assert(B == 8, "the accesses by row take blocks of 8 steps");
+            for (int s0 = (wave - 2 - kG2Writers) * B; s0 < S8; s0 += kG2Loaders * B) {
+                uint32_t it = 0;
+                bool quit = false;
+                for (;;) {
+                    int m = INT_MAX;
+#pragma unroll
+                    for (int k = 0; k < kG2Writers; ++k) m = min(m, lds_load(s_prog + k));
+                    if (m >= s0 + B - kG2Ring) break;
+                    if (spun_out(it, false)) {
+                        quit = true;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                if (quit) break;
+                Pair<T> cv[B];
+                T bv[B], pv[B];
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    const int s = s0 + u;
+                    const bool in = s < G.S;
+                    const T *cp = coef + ((int64_t)c * G.S + (in ? s : 0)) * NC2 * 64;
+                    cv[u] = in ? ((const Pair<T> *)cp)[lane] : Pair<T>{};
+                    if constexpr (UPPER) pv[u] = in ? cp[128 + lane] : (T)0;
+                    const int64_t at = io.bpad ? row_of(lane, s - lane) >= 0 ? p0 + s * pd : -1
+                                               : row_of(acc_col(u), s0 + acc_step(u) - acc_col(u));
+                    bv[u] = at >= 0 ? io.b[at] : (T)0;
+                }
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    const int o = ((s0 + u) & RM) * 64 + lane;
+                    cpr[o] = cv[u];
+                    if constexpr (UPPER) rpv[o] = pv[u];
+                }
+                T *const rb = rhs + (s0 & RM) * kG2Row;
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+                    rb[io.bpad ? u * kG2Row + lane : acc_step(u) * kG2Row + acc_col(u)] = bv[u];
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if (lane < B)
+                    __hip_atomic_store(&filled[(s0 + lane) & RM], s0 + lane, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {  // the last workgroup out resets the counters for the next launch
+        const uint32_t d = atomicAdd(&sync[1], 1u);
+        if (d == gridDim.x - 1) {
+            __hip_atomic_store(&sync[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
+// Packed coefficients of a wavefront plan: the value map[..] of the factor (0 where it
+// is negative); the plan's slot 3 is the pivot, stored as its reciprocal. 3D grid: the
+// plan's own layout, [step][k][lane]. 2D grid (flat), whose slot 1 is empty: per step the
+// pairs (slot 0, slot 2) of the 64 lanes, then slot 3 of each.
+template <class T>
+__global__ __launch_bounds__(256) void k_grid_coef(size_t n, int ncoef, int flat, const int32_t *__restrict__ map,
                                                    const double *__restrict__ src, T *__restrict__ out) {
     const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n) return;
-    const int32_t m = map[q];
-    const int k = (int)((q / 64) % (size_t)ncoef);
+    const size_t per = 64 * (size_t)(ncoef - flat), step = q / per;
+    const int r = (int)(q % per);
+    int k = r / 64, lane = r % 64;
+    if (flat) {
+        k = r >= 128 ? 3 : (r & 1) ? 2 : 0;
+        lane = r >= 128 ? r - 128 : r / 2;
+    }
+    const int32_t m = map[(step * ncoef + k) * 64 + lane];
     T v = m >= 0 ? (T)src[m] : (T)0;
     if (k == 3 && m >= 0) v = (T)1 / v;
     out[q] = v;
@@ -1380,22 +1734,19 @@ void launch_grid(const hec_grid &g, uint32_t *sync, uint32_t *err, const GridIO<
     else
         coef = g.coef32.get();
     const int grid = std::min(nclaims, 1024);
-    auto go = [&](auto ta) {
-        constexpr int TA = decltype(ta)::value;
-        constexpr size_t lds = grid_lds_bytes<T, UPPER, TA>();
-        static_assert(lds <= 160 * 1024, "LDS");
-        static bool attr_set = false;  // one per instantiation
+    auto go = [&](auto kernel, size_t lds, int waves, bool &attr_set) {
         if (!attr_set) {
-            HEC_HIP(hipFuncSetAttribute((const void *)k_trsv_grid<T, UPPER, TA>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            HEC_HIP(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
             attr_set = true;
         }
-        k_trsv_grid<T, UPPER, TA><<<grid, 64 * kGridWaves, lds, s>>>(G, coef, io, sync, skip);
+        kernel<<<grid, 64 * waves, lds, s>>>(G, coef, io, sync, skip);
     };
+    static bool attr3 = false, attr2 = false;  // one per instantiation
+    static_assert(grid_lds_bytes<T, UPPER>() <= 160 * 1024 && grid2_lds_bytes<T, UPPER>() <= 160 * 1024, "LDS");
     if (g.TA == plan::kGT)
-        go(std::integral_constant<int, plan::kGT>());
+        go(k_trsv_grid<T, UPPER>, grid_lds_bytes<T, UPPER>(), kGridWaves, attr3);
     else
-        go(std::integral_constant<int, plan::kGT2>());
+        go(k_trsv_grid2<T, UPPER>, grid2_lds_bytes<T, UPPER>(), kG2Waves, attr2);
     HEC_CHECK_LAUNCH();
 }
 
@@ -1520,15 +1871,16 @@ void build_grid(const hec_ilu_s &M, bool upper, hec_grid &g, hipStream_t s) {
     g.sa = P.sa;
     g.sb = P.sb;
     g.sc = P.sc;
-    const size_t m = P.src.size();
-    DevBuf<int32_t> dsrc(m);
-    dsrc.upload(P.src.data(), m, s);
+    const int flat = P.TA == plan::kGT2 ? 1 : 0;
+    DevBuf<int32_t> dsrc(P.src.size());
+    dsrc.upload(P.src.data(), P.src.size(), s);
+    const size_t m = P.src.size() / P.ncoef * (P.ncoef - flat);
     g.coef.alloc(m);
-    k_grid_coef<double><<<ceil_div(m, 256), 256, 0, s>>>(m, P.ncoef, dsrc.get(), M.LUx.get(), g.coef.get());
+    k_grid_coef<double><<<ceil_div(m, 256), 256, 0, s>>>(m, P.ncoef, flat, dsrc.get(), M.LUx.get(), g.coef.get());
     HEC_CHECK_LAUNCH();
     if (M.has_f32) {
         g.coef32.alloc(m);
-        k_grid_coef<float><<<ceil_div(m, 256), 256, 0, s>>>(m, P.ncoef, dsrc.get(), M.LUx.get(), g.coef32.get());
+        k_grid_coef<float><<<ceil_div(m, 256), 256, 0, s>>>(m, P.ncoef, flat, dsrc.get(), M.LUx.get(), g.coef32.get());
         HEC_CHECK_LAUNCH();
     }
     HEC_HIP(hipStreamSynchronize(s));  // dsrc and the host map end here

@@ -1,0 +1,54 @@
+"""GPU parity of the wavefront triangular solve on 2D grids at the edges of its tiles (64 columns)
+and blocks (8 steps), columns along either axis, against the componentwise backward error of
+substitution; an infinite right-hand side reaches exactly the rows that depend on it."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1606_00545_amd import hec, synth
+from tests._gpu import dev, empty, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("shape", [(16, 17), (63, 64), (64, 65), (66, 65), (127, 130), (129, 128), (193, 321), (321, 193)])
+def test_tile_edges(shape, f32):
+    import scipy.sparse as sp
+    import torch
+    A = synth.lognormal_tpfa(shape, 1.0, np.random.default_rng(shape[0]))
+    M = hec.ilu_factor(A, k=0, keep_f32=True)
+    lv = hec.level_schedule(M)
+    assert hec.levels_grid(lv)
+    LUp, LUj, LUx = hec.ilu_export(M)
+    u, dt = (2.0 ** -24, torch.float32) if f32 else (2.0 ** -53, torch.float64)
+    S = sp.csr_matrix((LUx.astype(np.float32).astype(np.float64) if f32 else LUx, LUj, LUp), shape=(A.n, A.n))
+    L, U = sp.tril(S, -1).tocsr() + sp.eye(A.n), sp.triu(S).tocsr()
+    b = dev(np.random.default_rng(A.n).uniform(-1, 1, A.n), dt)
+    y, z, x, x2 = (empty(A.n, "f32" if f32 else "f64") for _ in range(4))
+    hec.trsv_levels(M, lv, b, x2, hec.LU)
+    hec.trsv_levels(M, lv, b, y, hec.LOWER)
+    hec.trsv_levels(M, lv, y, z, hec.UPPER)
+    hec.trsv_levels(M, lv, b, x, hec.LU)
+    hec.levels_check(lv)
+    b, y, z, x, x2 = (host(v).astype(np.float64) for v in (b, y, z, x, x2))
+    assert np.array_equal(x, z) and np.array_equal(x, x2)  # the chain is the two solves, and repeats
+    gam = 8 * u  # two products and subtractions, the reciprocal pivot and its product, doubled
+    assert (np.abs(b - L @ y) <= gam * (abs(L) @ np.abs(y) + np.abs(b))).all()
+    assert (np.abs(y - U @ z) <= gam * (abs(U) @ np.abs(z) + np.abs(y))).all()
+
+
+@pytest.mark.parametrize("shape", [(70, 90), (90, 70)])
+def test_infinity_stays_in_its_cone(shape):
+    A = synth.lognormal_tpfa(shape, 1.0, np.random.default_rng(3))
+    M = hec.ilu_factor(A, k=0)
+    lv = hec.level_schedule(M)
+    nx, ny = shape
+    b = np.random.default_rng(4).uniform(-1, 1, A.n)
+    i, j = nx - 5, ny - 7
+    b[i + nx * j] = np.inf
+    F = O.iluk(A.n, A.Ap, A.Aj, A.Ax, 0)
+    y = empty(A.n)
+    hec.trsv_levels(M, lv, dev(b), y, hec.LOWER)
+    hec.levels_check(lv)
+    assert np.array_equal(np.isfinite(host(y)), np.isfinite(O.trsv_lower(F, b)))
