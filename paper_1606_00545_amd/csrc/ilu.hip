@@ -2,8 +2,8 @@
 // Eq. (11), Alg. 3), plus their C entry points and trsv_levels'.
 //
 // Symbolic work (the fill pattern S_k, the levels) is integer work done once
-// per matrix on the host. The numeric factorisation runs on the device, one
-// launch per level of L.
+// per matrix on the host. The numeric factorisation runs on the device, in one
+// launch whose rows wait for the rows they eliminate with.
 #include <algorithm>
 #include <cmath>
 #include <memory>
@@ -66,10 +66,193 @@ static void symbolic_iluk(int32_t n, const int32_t *Ap, const int32_t *Aj, int32
 
 // ------------------------------------------------------------------ numeric ILU kernel
 
-// Rows of one level of L, one thread per row (Alg. 2 restricted to S_k):
-// for each stored p < i in ascending order, l_ip = a_ip / u_pp, then
-// a_ij -= l_ip * u_pj for every stored (p, j), j > p, that is also in row i.
-// All rows p were finished by earlier launches.
+// Numeric elimination (Alg. 2 restricted to S_k) in one launch. G lanes take a row i,
+// 64 / G rows of one level of L a wavefront: for each stored p < i in ascending order,
+// l_ip = a_ip / u_pp, then a_ij -= l_ip * u_pj for every stored (p, j), j > p, that is
+// also in row i, the lanes taking the entries of row p. Row i is worked on in LDS and
+// written to `out` once; `out` starts filled with a signalling NaN that arithmetic never
+// produces, so an entry of row p is polled until it is final (device-coherent accesses).
+// Workgroups claim items (rows q0 .. q0 + cnt - 1 of perm, the level order) from a ticket
+// counter, the next claim on its way meanwhile: an item only waits for items of earlier
+// levels, claimed before it by running workgroups.
+//
+// Bound: the chain of levels, each a store and a load between compute units and one
+// division and update per pivot. With a launch per level and one thread per row, its
+// loads one after another, a level took 15 us (60^3 ILU(0), 178 levels: 2.7 ms), 45 us
+// with ILU(1) rows and 9.5 ms with rows of up to 512 entries (60,000-row power-law
+// matrix: 285 ms); now 0.56, 2.8 (75 x 62 x 51 ILU(1), 15.4 ms before) and 1.5 ms in all.
+// The values are the same bit for bit.
+constexpr uint32_t kIluSpin = 1u << 26;  // polls of a wait before the factorisation gives up
+constexpr unsigned long long kIluSent = 0x7FF4DEADBEEF1234ull;
+constexpr int kIluCap16 = 96, kIluCap64 = 512;  // longest rows of the two widths (LDS per row)
+
+struct IluArgs {
+    int32_t nitems;
+    const int2 *items;
+    const int32_t *perm, *LUp, *LUj, *diag;
+    const double *in;
+    double *out;
+    int32_t *zero_pivot;
+    uint32_t *sync, *err;  // ticket; set when a wait gave up
+};
+
+template <int G>
+constexpr size_t ilu_lds_bytes() {
+    return (size_t)4 * (64 / G) * (G == 16 ? kIluCap16 : kIluCap64) * (sizeof(double) + 3 * sizeof(int32_t));
+}
+
+template <int G>
+__global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
+    using U = unsigned long long;
+    constexpr int CAP = G == 16 ? kIluCap16 : kIluCap64;
+    extern __shared__ __align__(16) char ism[];
+    __shared__ int s_claim[2], s_abort[2];  // by the round's parity
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane % G, grp = threadIdx.x / G;
+    double *const vals = (double *)ism + grp * CAP;  // the group's row: values, columns, and per
+    int32_t *const cols = (int32_t *)((double *)ism + 4 * (64 / G) * CAP) + grp * 3 * CAP;
+    int32_t *const pdiag = cols + CAP, *const pend = cols + 2 * CAP;  // pivot: its diagonal, its row's end
+    auto poll = [&](const double *p) {
+        return __hip_atomic_load((const U *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto gave_up = [&](uint32_t &it) {  // one more poll of a wait (wave-uniform)
+        ++it;
+        if (it > kIluSpin) return true;
+        if ((it & 63) == 0 && __hip_atomic_load(A.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return true;
+        __builtin_amdgcn_s_sleep(1);
+        return false;
+    };
+    auto lds_order = [] {  // LDS accesses of one wavefront complete in order: only the compiler is held
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+    };
+    struct Piv {  // pivot row p: this lane's entry u of its upper part, its place in row i, and u_pp
+        int32_t u, pe, f;
+        U v, d;
+        const double *pv, *pd;
+    };
+    constexpr int NP = 4;  // pivots whose entries are waited for together
+    // false: a wait gave up
+    auto factor = [&](int32_t q0, int32_t cnt) {
+        const bool live = lane / G < cnt;
+        const int32_t i = A.perm[q0 + (live ? lane / G : 0)];
+        const int32_t b0 = A.LUp[i], len = live ? A.LUp[i + 1] - b0 : 0, nl = live ? A.diag[i] - b0 : 0;
+        for (int e = g; e < len; e += G) {
+            const int32_t c = A.LUj[b0 + e];
+            cols[e] = c;
+            vals[e] = A.in[b0 + e];
+            if (e < nl) {
+                pdiag[e] = A.diag[c];
+                pend[e] = A.LUp[c + 1];
+            }
+        }
+        lds_order();
+        auto place = [&](int e, int32_t j) -> int32_t {  // of column j in row i past entry e, -1: not stored
+            int lo = e + 1, hi = len;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (cols[mid] < j) lo = mid + 1;
+                else hi = mid;
+            }
+            return lo < len && cols[lo] == j ? lo : -1;
+        };
+        // entry u of pivot e's row (only looked up where row i has its column)
+        auto load = [&](int e, int32_t u, bool in, Piv &P) {
+            P.u = u;
+            P.f = in && u < P.pe ? place(e, A.LUj[u]) : -1;
+            P.v = 0;
+            if (P.f >= 0) {
+                P.pv = A.out + u;
+                P.v = poll(P.pv);
+            }
+        };
+        bool stop = false;  // the row met a zero pivot: the rest of it stays as it is
+        for (int e0 = 0; __ballot(e0 < nl) != 0; e0 += NP) {
+            Piv P[NP];
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const bool in = e0 + k < nl;
+                P[k].pe = in ? pend[e0 + k] : 0;
+                P[k].pd = P[k].pv = A.out + (in ? pdiag[e0 + k] : 0);
+                P[k].d = in ? poll(P[k].pd) : 0;
+                load(e0 + k, in ? pdiag[e0 + k] + 1 + g : 0, in, P[k]);
+            }
+            uint32_t it = 0;
+            for (;;) {  // until the entries of all NP pivots are final; only the pending ones are loaded again
+                bool pend = false;
+#pragma unroll
+                for (int k = 0; k < NP; ++k) pend |= P[k].v == kIluSent || P[k].d == kIluSent;
+                if (__ballot(pend) == 0) break;
+                if (gave_up(it)) return false;
+#pragma unroll
+                for (int k = 0; k < NP; ++k) {
+                    if (P[k].v == kIluSent) P[k].v = poll(P[k].pv);
+                    if (P[k].d == kIluSent) P[k].d = poll(P[k].pd);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const int e = e0 + k;
+                const double upp = __longlong_as_double((long long)P[k].d);
+                if (e < nl && !stop && upp == 0.0) {
+                    if (g == 0) atomicMax(A.zero_pivot, cols[e] + 1);
+                    stop = true;
+                }
+                const bool act = e < nl && !stop;
+                const double lip = act ? vals[e] / upp : 0.0;
+                lds_order();
+                if (act && g == 0) vals[e] = lip;
+                if (act && P[k].f >= 0) vals[P[k].f] -= lip * __longlong_as_double((long long)P[k].v);
+                // entries of row p past the first G
+                for (int32_t u = P[k].u + G; __ballot(act && u < P[k].pe) != 0; u += G) {
+                    load(e, u, act, P[k]);
+                    it = 0;
+                    while (__ballot(P[k].v == kIluSent) != 0) {
+                        if (gave_up(it)) return false;
+                        if (P[k].v == kIluSent) P[k].v = poll(P[k].pv);
+                    }
+                    if (act && P[k].f >= 0) vals[P[k].f] -= lip * __longlong_as_double((long long)P[k].v);
+                }
+                lds_order();
+            }
+        }
+        for (int e = g; e < len; e += G) {
+            U v = (U)__double_as_longlong(vals[e]);
+            if (v == kIluSent) v = 0x7FF8000000000000ull;  // an input that is the sentinel: a quiet NaN
+            __hip_atomic_store((U *)(A.out + b0 + e), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        lds_order();
+        return true;
+    };
+    if (threadIdx.x == 0) {
+        s_abort[0] = s_abort[1] = 0;
+        s_claim[0] = (int)atomicAdd(A.sync, 1u);
+    }
+    for (int round = 0;; ++round) {
+        __syncthreads();
+        const int c = s_claim[round & 1];
+        if (s_abort[round & 1] || (int64_t)c * 4 >= A.nitems) break;  // uniform: read after the barrier
+        uint32_t next = 0;
+        if (threadIdx.x == 0) next = atomicAdd(A.sync, 1u);
+        const int t = c * 4 + wave;
+        if (t < A.nitems) {
+            const int2 item = A.items[t];
+            if (!factor(__builtin_amdgcn_readfirstlane(item.x), __builtin_amdgcn_readfirstlane(item.y))) {
+                __hip_atomic_store(A.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_abort[(round + 1) & 1] = 1;
+            }
+        }
+        if (threadIdx.x == 0) s_claim[(round + 1) & 1] = (int)next;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_ilu_fill(size_t n, double *__restrict__ out) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) ((unsigned long long *)out)[i] = kIluSent;
+}
+
+// Rows longer than k_ilu_rows keeps in LDS: the rows of one level of L a launch, one
+// thread per row, in place; all rows p were finished by earlier launches.
 __global__ __launch_bounds__(256) void k_ilu_level(int32_t cnt, const int32_t *__restrict__ rows,
                                                    const int32_t *__restrict__ LUp,
                                                    const int32_t *__restrict__ LUj,
@@ -143,22 +326,56 @@ static std::unique_ptr<hec_ilu_s> factor_csr(int32_t n, const int32_t *Ap, const
     M->LUp.upload(M->hLUp.data(), n + 1, s);
     M->LUj.upload(M->hLUj.data(), M->nnz, s);
     M->diag.upload(M->hdiag.data(), n, s);
-    M->LUx.upload(x0.data(), M->nnz, s);
-    // numeric elimination, one launch per level of L
-    std::vector<int32_t> lptr, perm;
+    // numeric elimination in level order of L
+    std::vector<int32_t> lptr, perm, items;
     int32_t nlev = plan::compute_levels(n, M->hLUp.data(), M->hLUj.data(), M->hdiag.data(), false, lptr, perm);
-    DevBuf<int32_t> dperm(n), dflag(1);
+    int32_t maxlen = 0;
+    for (int32_t i = 0; i < n; ++i) maxlen = std::max(maxlen, M->hLUp[i + 1] - M->hLUp[i]);
+    enum : int { FLAG = 0, TICKET = 1, ERR = 2, NFLAGS = 4 };  // zero pivot (row + 1), claims, given up
+    DevBuf<int32_t> dperm(n), dflag(NFLAGS), ditems;
+    DevBuf<double> din;
     dperm.upload(perm.data(), n, s);
-    HEC_HIP(hipMemsetAsync(dflag.get(), 0, sizeof(int32_t), s));
-    for (int32_t l = 1; l < nlev; ++l) {  // level 0 rows have no L entries: nothing to do
-        int32_t a = lptr[l], cnt = lptr[l + 1] - lptr[l];
-        k_ilu_level<<<ceil_div(cnt, 256), 256, 0, s>>>(cnt, dperm.get() + a, M->LUp.get(), M->LUj.get(),
-                                                       M->diag.get(), M->LUx.get(), dflag.get());
-        HEC_CHECK_LAUNCH();
+    HEC_HIP(hipMemsetAsync(dflag.get(), 0, NFLAGS * sizeof(int32_t), s));
+    if (maxlen <= kIluCap64) {
+        const bool narrow = maxlen <= kIluCap16;
+        const int32_t per = narrow ? 4 : 1;  // rows of a wavefront: 16 or 64 lanes each
+        for (int32_t l = 0; l < nlev; ++l)
+            for (int32_t q = lptr[l]; q < lptr[l + 1]; q += per)
+                items.insert(items.end(), {q, std::min(per, lptr[l + 1] - q)});
+        ditems.alloc(items.size());
+        ditems.upload(items.data(), items.size(), s);
+        din.alloc(M->nnz);
+        din.upload(x0.data(), M->nnz, s);
+        if (M->nnz) {
+            k_ilu_fill<<<ceil_div(M->nnz, 256), 256, 0, s>>>(M->nnz, M->LUx.get());
+            HEC_CHECK_LAUNCH();
+        }
+        const int32_t nitems = (int32_t)(items.size() / 2);
+        const IluArgs args{nitems,          (const int2 *)ditems.get(), dperm.get(), M->LUp.get(), M->LUj.get(),
+                           M->diag.get(),   din.get(),                  M->LUx.get(), dflag.get() + FLAG,
+                           (uint32_t *)dflag.get() + TICKET, (uint32_t *)dflag.get() + ERR};
+        const unsigned grid = std::min(ceil_div(nitems, 4), 1024u);
+        if (nitems) {
+            if (narrow)
+                k_ilu_rows<16><<<grid, 256, ilu_lds_bytes<16>(), s>>>(args);
+            else
+                k_ilu_rows<64><<<grid, 256, ilu_lds_bytes<64>(), s>>>(args);
+            HEC_CHECK_LAUNCH();
+        }
+    } else {
+        M->LUx.upload(x0.data(), M->nnz, s);
+        for (int32_t l = 1; l < nlev; ++l) {  // level 0 rows have no L entries: nothing to do
+            int32_t a = lptr[l], cnt = lptr[l + 1] - lptr[l];
+            k_ilu_level<<<ceil_div(cnt, 256), 256, 0, s>>>(cnt, dperm.get() + a, M->LUp.get(), M->LUj.get(),
+                                                           M->diag.get(), M->LUx.get(), dflag.get());
+            HEC_CHECK_LAUNCH();
+        }
     }
-    int32_t zp = 0;
-    dflag.download(&zp, 1, s);
+    int32_t hflag[NFLAGS] = {};
+    dflag.download(hflag, NFLAGS, s);
     HEC_HIP(hipStreamSynchronize(s));
+    if (hflag[ERR]) fail(HEC_ERR_TIMEOUT, "a wait of the ILU factorisation gave up");
+    int32_t zp = hflag[FLAG];
     if (zp) fail(HEC_ERR_ZERO_PIVOT, "zero pivot in row " + std::to_string(zp - 1));
     // every pivot u_ii must be nonzero for the backward substitution, also
     // those of rows that no later row uses
