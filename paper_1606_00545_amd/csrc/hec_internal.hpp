@@ -233,6 +233,7 @@ struct hec_ilu_s {
     bool has_f32 = false;
     std::vector<int32_t> hLUp, hLUj;  // host copy of the pattern S_k (used by level_schedule)
     std::vector<int32_t> hdiag;       // position of the diagonal in each row
+    std::vector<int32_t> hlptr, hlperm;  // levels of L (Eq. (11)): start pointers, rows by (level, row)
     hec::DevBuf<int32_t> LUp, LUj, diag;
     hec::DevBuf<double> LUx;
     hec::DevBuf<float> LUx32;
@@ -357,8 +358,9 @@ void trsv_launch(const hec_levels_s &lv, uint32_t which, const T *b, T *x, hipSt
 // Sets the internal lower-solve outputs of lv to the sentinel (once, after allocation).
 void trsv_init_levels(hec_levels_s &lv, hipStream_t s);
 
-// Builds tri.grid (the wavefront plan) when the factor's triangle admits one.
-void build_grid(const hec_ilu_s &M, bool upper, hec_grid &g, hipStream_t s);
+// Builds the wavefront plans of both triangles when the factor admits them (else both
+// stay off): the pattern is checked and the coefficients are packed on the device.
+void build_grid(const hec_ilu_s &M, hec_grid &lower, hec_grid &upper, hipStream_t s);
 
 // Only the level schedule of a triangle (Eq. (11), Alg. 3): nlev, hlevel_ptr, hperm.
 void level_only(const hec_ilu_s &M, bool upper, hec_tri &tri);

@@ -310,15 +310,19 @@ static std::unique_ptr<hec_ilu_s> factor_csr(int32_t n, const int32_t *Ap, const
     symbolic_iluk(n, Ap, Aj, k, M->hLUp, M->hLUj, M->hdiag);
     plan::detect_grid(n, Ap, Aj, M->gnx, M->gny, M->gnz);
     M->nnz = M->hLUp[n];
-    // A's values scattered into S_k, fill entries start at 0
-    std::vector<double> x0(M->nnz, 0.0);
-    for (int32_t i = 0; i < n; ++i) {
-        int32_t f = M->hLUp[i];
-        for (int32_t e = Ap[i]; e < Ap[i + 1]; ++e) {
-            while (M->hLUj[f] < Aj[e]) ++f;
-            x0[f] = Ax[e];
+    // A's values scattered into S_k, fill entries start at 0 (k = 0: S_0 is A's pattern)
+    std::vector<double> scat;
+    if (M->nnz != Ap[n]) {
+        scat.assign(M->nnz, 0.0);
+        for (int32_t i = 0; i < n; ++i) {
+            int32_t f = M->hLUp[i];
+            for (int32_t e = Ap[i]; e < Ap[i + 1]; ++e) {
+                while (M->hLUj[f] < Aj[e]) ++f;
+                scat[f] = Ax[e];
+            }
         }
     }
+    const double *x0 = scat.empty() ? Ax : scat.data();
     M->LUp.alloc(n + 1);
     M->LUj.alloc(M->nnz);
     M->diag.alloc(n);
@@ -327,7 +331,7 @@ static std::unique_ptr<hec_ilu_s> factor_csr(int32_t n, const int32_t *Ap, const
     M->LUj.upload(M->hLUj.data(), M->nnz, s);
     M->diag.upload(M->hdiag.data(), n, s);
     // numeric elimination in level order of L
-    std::vector<int32_t> lptr, perm, items;
+    std::vector<int32_t> &lptr = M->hlptr, &perm = M->hlperm, items;
     int32_t nlev = plan::compute_levels(n, M->hLUp.data(), M->hLUj.data(), M->hdiag.data(), false, lptr, perm);
     int32_t maxlen = 0;
     for (int32_t i = 0; i < n; ++i) maxlen = std::max(maxlen, M->hLUp[i + 1] - M->hLUp[i]);
@@ -339,13 +343,16 @@ static std::unique_ptr<hec_ilu_s> factor_csr(int32_t n, const int32_t *Ap, const
     if (maxlen <= kIluCap64) {
         const bool narrow = maxlen <= kIluCap16;
         const int32_t per = narrow ? 4 : 1;  // rows of a wavefront: 16 or 64 lanes each
+        items.reserve(2 * ((size_t)n / per + nlev));
         for (int32_t l = 0; l < nlev; ++l)
-            for (int32_t q = lptr[l]; q < lptr[l + 1]; q += per)
-                items.insert(items.end(), {q, std::min(per, lptr[l + 1] - q)});
+            for (int32_t q = lptr[l]; q < lptr[l + 1]; q += per) {
+                items.push_back(q);
+                items.push_back(std::min(per, lptr[l + 1] - q));
+            }
         ditems.alloc(items.size());
         ditems.upload(items.data(), items.size(), s);
         din.alloc(M->nnz);
-        din.upload(x0.data(), M->nnz, s);
+        din.upload(x0, M->nnz, s);
         if (M->nnz) {
             k_ilu_fill<<<ceil_div(M->nnz, 256), 256, 0, s>>>(M->nnz, M->LUx.get());
             HEC_CHECK_LAUNCH();
@@ -363,7 +370,7 @@ static std::unique_ptr<hec_ilu_s> factor_csr(int32_t n, const int32_t *Ap, const
             HEC_CHECK_LAUNCH();
         }
     } else {
-        M->LUx.upload(x0.data(), M->nnz, s);
+        M->LUx.upload(x0, M->nnz, s);
         for (int32_t l = 1; l < nlev; ++l) {  // level 0 rows have no L entries: nothing to do
             int32_t a = lptr[l], cnt = lptr[l + 1] - lptr[l];
             k_ilu_level<<<ceil_div(cnt, 256), 256, 0, s>>>(cnt, dperm.get() + a, M->LUp.get(), M->LUj.get(),
@@ -595,12 +602,7 @@ hec_status level_schedule(hec_ilu M, void *stream, hec_levels *out) {
         lv->nf = M->n;
         lv->ras = !M->hext_row.empty();
         if (!lv->ras && trsv_grid_enabled()) {  // the wavefront plans: both triangles or neither
-            build_grid(*M, true, lv->upper.grid, s);
-            if (lv->upper.grid.on) build_grid(*M, false, lv->lower.grid, s);
-            const hec_grid &gl = lv->lower.grid, &gu = lv->upper.grid;
-            if (gl.on && (gl.PA != gu.PA || gl.PB != gu.PB || gl.S != gu.S))  // (one padded order serves both)
-                lv->lower.grid = hec_grid();
-            if (!lv->lower.grid.on) lv->upper.grid = hec_grid();
+            build_grid(*M, lv->lower.grid, lv->upper.grid, s);
         }
         if (lv->lower.grid.on) {  // the level schedules only (levels_export, the batched copies)
             level_only(*M, true, lv->upper);

@@ -676,12 +676,10 @@ HEC_HD inline GridCell grid_cell(int32_t NA, int32_t NB, int32_t NC, int32_t PA,
     return g;
 }
 
-// Builds the wavefront plan of the strict lower (upper) triangle of the factor pattern
-// on the nx x ny x nz grid. Returns false (G untouched) when it does not apply: no
-// grid, fewer than kGT columns along a tile axis of a 3D grid (kGT2Min along a of a
-// 2D one), or an entry that is not one of the neighbours behind its row.
-inline bool make_grid_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, const int32_t *diag, int32_t gnx,
-                           int32_t gny, int32_t gnz, bool upper, GridPlan &G) {
+// The shape of the wavefront plan of one triangle on the nx x ny x nz grid: everything but
+// `src`. Returns false (G untouched) when none applies: no grid, or fewer than kGT columns
+// along a tile axis of a 3D grid (kGT2Min along a of a 2D one).
+inline bool grid_plan_shape(int32_t n, int32_t gnx, int32_t gny, int32_t gnz, bool upper, GridPlan &G) {
     if (gnx <= 0 || gny <= 0 || gnz <= 0 || (int64_t)gnx * gny * gnz != n) return false;
     const int32_t ext[3] = {gnx, gny, gnz};
     const int64_t str[3] = {1, gnx, (int64_t)gnx * gny};
@@ -691,6 +689,34 @@ inline bool make_grid_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, co
     const int a = c == 0 ? 1 : 0, b = c == 2 ? 1 : 2;  // the others, by stride
     const bool flat = ext[b] == 1;  // a 2D grid (b the unit axis): tiles of 64 x 1
     if (flat ? ext[a] < kGT2Min : ext[a] < kGT || ext[b] < kGT) return false;
+    GridPlan P;
+    P.NA = ext[a];
+    P.NB = ext[b];
+    P.NC = ext[c];
+    P.sa = str[a];
+    P.sb = str[b];
+    P.sc = str[c];
+    P.TA = flat ? kGT2 : kGT;
+    P.TB = 64 / P.TA;
+    P.PA = (P.NA + P.TA - 1) / P.TA;
+    P.PB = (P.NB + P.TB - 1) / P.TB;
+    P.S = P.NC + (P.TA - 1) + (P.TB - 1);
+    P.ncoef = upper ? kGridCoefUpper : kGridCoefLower;
+    G = std::move(P);
+    return true;
+}
+
+// Builds the wavefront plan of the strict lower (upper) triangle of the factor pattern
+// with its coefficient map, on the host (the library checks the pattern and packs the
+// coefficients on the device; the plan checks replay this map). Returns false (G untouched)
+// when it does not apply: no shape, or an entry that is not one of the neighbours behind
+// its row.
+inline bool make_grid_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, const int32_t *diag, int32_t gnx,
+                           int32_t gny, int32_t gnz, bool upper, GridPlan &G) {
+    GridPlan P;
+    if (!grid_plan_shape(n, gnx, gny, gnz, upper, P)) return false;
+    const int32_t ext[3] = {gnx, gny, gnz};
+    const int64_t str[3] = {1, gnx, (int64_t)gnx * gny};
     // every strict-triangle entry must be a neighbour behind the row
     for (int32_t i = 0; i < n; ++i) {
         const int32_t co[3] = {i % gnx, (i / gnx) % gny, i / (gnx * gny)};
@@ -705,19 +731,6 @@ inline bool make_grid_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, co
             if (!ok) return false;
         }
     }
-    GridPlan P;
-    P.NA = ext[a];
-    P.NB = ext[b];
-    P.NC = ext[c];
-    P.sa = str[a];
-    P.sb = str[b];
-    P.sc = str[c];
-    P.TA = flat ? kGT2 : kGT;
-    P.TB = 64 / P.TA;
-    P.PA = (P.NA + P.TA - 1) / P.TA;
-    P.PB = (P.NB + P.TB - 1) / P.TB;
-    P.S = P.NC + (P.TA - 1) + (P.TB - 1);
-    P.ncoef = upper ? kGridCoefUpper : kGridCoefLower;
     const int64_t nc = P.nclaims();
     P.src.assign((size_t)(nc * P.S * P.ncoef * 64), -1);
     const int64_t sg = upper ? 1 : -1;

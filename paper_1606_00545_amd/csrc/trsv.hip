@@ -1616,26 +1616,65 @@ __global__ __launch_bounds__(64 * kG2Waves) void k_trsv_grid2(GridArgs G, const 
     }
 }
 
-// Packed coefficients of a wavefront plan: the value map[..] of the factor (0 where it
-// is negative); the plan's slot 3 is the pivot, stored as its reciprocal. 3D grid: the
-// plan's own layout, [step][k][lane]. 2D grid (flat), whose slot 1 is empty: per step the
-// pairs (slot 0, slot 2) of the 64 lanes, then slot 3 of each.
-template <class T>
-__global__ __launch_bounds__(256) void k_grid_coef(size_t n, int ncoef, int flat, const int32_t *__restrict__ map,
-                                                   const double *__restrict__ src, T *__restrict__ out) {
-    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const size_t per = 64 * (size_t)(ncoef - flat), step = q / per;
-    const int r = (int)(q % per);
-    int k = r / 64, lane = r % 64;
-    if (flat) {
-        k = r >= 128 ? 3 : (r & 1) ? 2 : 0;
-        lane = r >= 128 ? r - 128 : r / 2;
+// Whether every off-diagonal entry of the factor joins neighbours on the grid: *bad is set
+// where one does not.
+__global__ __launch_bounds__(256) void k_grid_check(int32_t n, int32_t nx, int32_t ny, int32_t nz,
+                                                    const int32_t *__restrict__ LUp, const int32_t *__restrict__ LUj,
+                                                    int32_t *bad) {
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t x = i % nx, y = (i / nx) % ny, z = i / (nx * ny);
+    bool ok = true;
+    for (int32_t e = LUp[i]; e < LUp[i + 1]; ++e) {
+        const int32_t d = LUj[e] - i, a = d < 0 ? -d : d;
+        if (d == 0) continue;
+        // (nx or ny may be 1: any of the axes an offset fits will do)
+        ok = ok && ((a == 1 && (d < 0 ? x > 0 : x + 1 < nx)) || (a == nx && (d < 0 ? y > 0 : y + 1 < ny)) ||
+                    (a == nx * ny && (d < 0 ? z > 0 : z + 1 < nz)));
     }
-    const int32_t m = map[(step * ncoef + k) * 64 + lane];
-    T v = m >= 0 ? (T)src[m] : (T)0;
-    if (k == 3 && m >= 0) v = (T)1 / v;
-    out[q] = v;
+    if (!ok) *bad = 1;
+}
+
+// Packed coefficients of a wavefront plan, one thread per step and lane: the factor's
+// values at the row's neighbours behind it (0 where it has none, or where the lane has no
+// row) and, for the upper triangle, the reciprocal of the pivot. 3D grid: [claim][step][k]
+// [lane] with k = back, below, left, reciprocal. 2D grid: per step the pairs (back, left)
+// of the 64 lanes, then the reciprocal of each.
+template <class T>
+__global__ __launch_bounds__(256) void k_grid_coef(int64_t total, int upper, int32_t NA, int32_t NB, int32_t NC,
+                                                   int32_t PA, int32_t PB, int TA, int32_t S, int64_t sa, int64_t sb,
+                                                   int64_t sc, const int32_t *__restrict__ LUp,
+                                                   const int32_t *__restrict__ LUj, const int32_t *__restrict__ diag,
+                                                   const double *__restrict__ LUx, T *__restrict__ out) {
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= total) return;
+    const int lane = (int)(q & 63);
+    const int64_t cs = q >> 6;  // claim * S + step
+    const int64_t claim = cs / S;
+    const plan::GridCell g = plan::grid_cell(NA, NB, NC, PA, PB, TA, upper != 0, claim, lane, (int32_t)(cs - claim * S));
+    T v[4] = {};
+    if (g.valid) {
+        const int64_t row = g.ga * sa + g.gb * sb + g.gc * sc;
+        const int64_t sg = upper ? 1 : -1;
+        const int32_t d = diag[row];
+        const int32_t e0 = upper ? d + 1 : LUp[row], e1 = upper ? LUp[row + 1] : d;
+        for (int32_t e = e0; e < e1; ++e) {
+            const int64_t o = (LUj[e] - row) * sg;
+            const T a = (T)LUx[e];
+            if (o == sc) v[0] = a;
+            else if (o == sb) v[1] = a;
+            else if (o == sa) v[2] = a;
+        }
+        if (upper) v[3] = (T)1 / (T)LUx[d];
+    }
+    if (TA == plan::kGT) {
+        T *const o = out + cs * 64 * (3 + upper) + lane;
+        for (int k = 0; k < 3 + upper; ++k) o[k * 64] = v[k];
+    } else {
+        T *const o = out + cs * 64 * (2 + upper);
+        ((Pair<T> *)o)[lane] = Pair<T>{v[0], v[2]};
+        if (upper) o[128 + lane] = v[3];
+    }
 }
 
 // Before a single-triangle solve: the output filled with the sentinel.
@@ -1852,39 +1891,56 @@ void trsv_init_levels(hec_levels_s &lv, hipStream_t s) {
 }
 
 void level_only(const hec_ilu_s &M, bool upper, hec_tri &tri) {
+    if (!upper) {  // kept from the factorisation
+        tri.nlev = (int32_t)M.hlptr.size() - 1;
+        tri.hlevel_ptr = M.hlptr;
+        tri.hperm = M.hlperm;
+        return;
+    }
     tri.nlev = plan::compute_levels(M.n, M.hLUp.data(), M.hLUj.data(), M.hdiag.data(), upper, tri.hlevel_ptr,
                                     tri.hperm);
 }
 
-void build_grid(const hec_ilu_s &M, bool upper, hec_grid &g, hipStream_t s) {
-    g = hec_grid();
-    plan::GridPlan P;
-    if (!plan::make_grid_plan(M.n, M.hLUp.data(), M.hLUj.data(), M.hdiag.data(), M.gnx, M.gny, M.gnz, upper, P))
-        return;
-    g.TA = P.TA;
-    g.NA = P.NA;
-    g.NB = P.NB;
-    g.NC = P.NC;
-    g.PA = P.PA;
-    g.PB = P.PB;
-    g.S = P.S;
-    g.sa = P.sa;
-    g.sb = P.sb;
-    g.sc = P.sc;
-    const int flat = P.TA == plan::kGT2 ? 1 : 0;
-    DevBuf<int32_t> dsrc(P.src.size());
-    dsrc.upload(P.src.data(), P.src.size(), s);
-    const size_t m = P.src.size() / P.ncoef * (P.ncoef - flat);
-    g.coef.alloc(m);
-    k_grid_coef<double><<<ceil_div(m, 256), 256, 0, s>>>(m, P.ncoef, flat, dsrc.get(), M.LUx.get(), g.coef.get());
+void build_grid(const hec_ilu_s &M, hec_grid &lower, hec_grid &upper, hipStream_t s) {
+    lower = hec_grid();
+    upper = hec_grid();
+    plan::GridPlan P[2];
+    for (int u = 0; u < 2; ++u)
+        if (!plan::grid_plan_shape(M.n, M.gnx, M.gny, M.gnz, u != 0, P[u])) return;
+    DevBuf<int32_t> bad(1);
+    int32_t hbad = 0;
+    HEC_HIP(hipMemsetAsync(bad.get(), 0, sizeof(int32_t), s));
+    k_grid_check<<<ceil_div(M.n, 256), 256, 0, s>>>(M.n, M.gnx, M.gny, M.gnz, M.LUp.get(), M.LUj.get(), bad.get());
     HEC_CHECK_LAUNCH();
-    if (M.has_f32) {
-        g.coef32.alloc(m);
-        k_grid_coef<float><<<ceil_div(m, 256), 256, 0, s>>>(m, P.ncoef, flat, dsrc.get(), M.LUx.get(), g.coef32.get());
-        HEC_CHECK_LAUNCH();
+    bad.download(&hbad, 1, s);
+    HEC_HIP(hipStreamSynchronize(s));
+    if (hbad) return;
+    for (int u = 0; u < 2; ++u) {
+        hec_grid &g = u ? upper : lower;
+        const plan::GridPlan &Q = P[u];
+        g.TA = Q.TA;
+        g.NA = Q.NA;
+        g.NB = Q.NB;
+        g.NC = Q.NC;
+        g.PA = Q.PA;
+        g.PB = Q.PB;
+        g.S = Q.S;
+        g.sa = Q.sa;
+        g.sb = Q.sb;
+        g.sc = Q.sc;
+        const int64_t total = g.pad_elems();
+        const int ncoef = Q.ncoef - (g.TA == plan::kGT2 ? 1 : 0);
+        auto pack = [&](auto &buf) {
+            buf.alloc((size_t)total * ncoef);
+            k_grid_coef<<<ceil_div(total, 256), 256, 0, s>>>(total, u, g.NA, g.NB, g.NC, g.PA, g.PB, g.TA, g.S, g.sa,
+                                                             g.sb, g.sc, M.LUp.get(), M.LUj.get(), M.diag.get(),
+                                                             M.LUx.get(), buf.get());
+            HEC_CHECK_LAUNCH();
+        };
+        pack(g.coef);
+        if (M.has_f32) pack(g.coef32);
+        g.on = true;
     }
-    HEC_HIP(hipStreamSynchronize(s));  // dsrc and the host map end here
-    g.on = true;
 }
 
 template void trsv_launch<double>(const hec_levels_s &, uint32_t, const double *, double *, hipStream_t,
