@@ -32,16 +32,16 @@
 // level): z = D^{-1} (b - A x), d = z / theta, then per sweep x += d and, before
 // the next, z -= D^{-1} A d and d = c1 d + c2 z with the recurrence's coefficients
 // (host scalars, the same for every cycle); one product with A per sweep.
-// A level whose rows are of about the same length (plain ELL wastes at most 30%
-// of its slab) is stored as plain ELL, so that one launch does a whole sweep
-// (the residual and the update, into a second vector); other levels keep the
-// HEC layout and sweep with an SpMV for the residual and an update. One cycle
-// with its residual norm is captured once into a HIP graph on the handle's own
-// stream and replayed.
+// Every operator is stored so that one launch does a whole step of the cycle (the
+// product with the operator and what follows from it, row by row): narrow rows of
+// about the same length as plain ELL, a thread per row; others as CSR, 2 to 64 lanes
+// per row. One cycle with its residual norm is captured once into a HIP graph on
+// the handle's own stream and replayed.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <memory>
+#include <mutex>
 #include <set>
 #include <vector>
 
@@ -324,58 +324,203 @@ std::vector<double> dense_inverse(const Csr &A) {
 
 namespace {
 
-// x += omega * dinv * r
-__global__ __launch_bounds__(256) void k_jacobi_update(int32_t n, double omega, const double *__restrict__ dinv,
-                                                       const double *__restrict__ r, double *__restrict__ x) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] += omega * dinv[i] * r[i];
+// ---------------------------------------------------------------- steps of a cycle
+// A step multiplies row i of an operator with x and hands the sum to an Op: prepare(i)
+// loads what the step needs beside the product (its loads go out before the row's), then
+// apply(i, sum, in) writes the results; with kReduce it returns a value whose squares the
+// workgroup adds. Bound: below some 100,000 rows the chain row pointer, column, x, result
+// inside a launch and the launch itself (2.5 to 4.5 us a step), above it the operator's
+// entries (62,500 rows of 18: 5 us). So a cycle is as fast as its steps are few: the
+// 50^3 Poisson cycle of six levels was 76 launches and 430 us with the product, the
+// residual and the update apart, and is 42 launches and 150 us. The coarse levels in one
+// workgroup with their vectors in LDS (295 and 57 rows: 43 us, their entries in registers,
+// against 28 us for the launches) were no gain.
+
+struct OpApply {  // y = M x
+    static constexpr bool kReduce = false;
+    struct In {};
+    double *y;
+    __device__ In prepare(int32_t) const { return {}; }
+    __device__ double apply(int32_t i, double s, const In &) const { y[i] = s; return 0.0; }
+};
+struct OpProlong {  // x += P xc
+    static constexpr bool kReduce = false;
+    struct In { double x; };
+    double *x;
+    __device__ In prepare(int32_t i) const { return {x[i]}; }
+    __device__ double apply(int32_t i, double s, const In &in) const { x[i] = in.x + s; return 0.0; }
+};
+template <bool NORM>
+struct OpResidual {  // r = b - A x; NORM: only ||r||^2
+    static constexpr bool kReduce = NORM;
+    struct In { double b; };
+    const double *b;
+    double *r;
+    __device__ In prepare(int32_t i) const { return {b[i]}; }
+    __device__ double apply(int32_t i, double s, const In &in) const {
+        const double v = in.b - s;
+        if constexpr (!NORM) r[i] = v;
+        return v;
+    }
+};
+struct OpJacobi {  // one damped Jacobi sweep: xo = xi + omega D^{-1} (b - A xi)
+    static constexpr bool kReduce = false;
+    struct In { double b, d, x; };
+    const double *b, *dinv, *xi;
+    double *xo;
+    double omega;
+    __device__ In prepare(int32_t i) const { return {b[i], dinv[i], xi[i]}; }
+    __device__ double apply(int32_t i, double s, const In &in) const {
+        xo[i] = in.x + omega * in.d * (in.b - s);
+        return 0.0;
+    }
+};
+struct OpRestrictJacobi {  // b_c = R r, and the coarse level's first sweep from zero: x = omega D^{-1} b_c
+    static constexpr bool kReduce = false;
+    struct In { double d; };
+    const double *dinv;
+    double *bc, *x;
+    double omega;
+    __device__ In prepare(int32_t i) const { return {dinv[i]}; }
+    __device__ double apply(int32_t i, double s, const In &in) const {
+        bc[i] = s;
+        x[i] = omega * in.d * s;
+        return 0.0;
+    }
+};
+struct OpRestrictCheb {  // b_c = R r, and the first Chebyshev sweep from zero: z = D^{-1} b_c, d = z / theta, x = d
+    static constexpr bool kReduce = false;
+    struct In { double d; };
+    const double *dinv;
+    double *bc, *z, *d, *x;
+    double theta;
+    __device__ In prepare(int32_t i) const { return {dinv[i]}; }
+    __device__ double apply(int32_t i, double s, const In &in) const {
+        const double zi = in.d * s, di = zi / theta;
+        bc[i] = s;
+        z[i] = zi;
+        d[i] = di;
+        x[i] = di;
+        return 0.0;
+    }
+};
+struct OpChebFirst {  // z = D^{-1} (b - A x), d = z / theta (x, which other rows read, takes d in the next sweep)
+    static constexpr bool kReduce = false;
+    struct In { double b, d; };
+    const double *b, *dinv;
+    double *z, *d;
+    double theta;
+    __device__ In prepare(int32_t i) const { return {b[i], dinv[i]}; }
+    __device__ double apply(int32_t i, double s, const In &in) const {
+        const double zi = in.d * (in.b - s);
+        z[i] = zi;
+        d[i] = zi / theta;
+        return 0.0;
+    }
+};
+struct OpChebStep {  // with the sum A d: z -= D^{-1} A d, d' = c1 d + c2 z; x takes d (if it has not), then in the last sweep d'
+    static constexpr bool kReduce = false;
+    struct In { double inv, z, d, x; };
+    const double *dinv, *di;
+    double *z, *dout, *x;
+    double c1, c2;
+    int32_t add_in, last;
+    __device__ In prepare(int32_t i) const { return {dinv[i], z[i], di[i], x[i]}; }
+    __device__ double apply(int32_t i, double s, const In &in) const {
+        const double zi = in.z - in.inv * s;
+        z[i] = zi;
+        const double dn = c1 * in.d + c2 * zi;
+        dout[i] = dn;
+        double xi = add_in ? in.x + in.d : in.x;
+        if (last) xi += dn;
+        x[i] = xi;
+        return 0.0;
+    }
+};
+
+// Sum of v^2 over the workgroup's rows, in a fixed order, to part[blockIdx.x].
+__device__ __forceinline__ void reduce_sq(double v, double *part) {
+    __shared__ double red[4];
+    double q = v * v;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = q;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// One damped Jacobi sweep on an ELL matrix (slab entry s of row i at s*ld + i):
-// xo = xi + omega * dinv * (b - A xi).
-__global__ __launch_bounds__(256) void k_jacobi_ell(int32_t n, int32_t K, int32_t ld, const int32_t *__restrict__ col,
-                                                    const double *__restrict__ val, const double *__restrict__ dinv,
-                                                    double omega, const double *__restrict__ xi,
-                                                    const double *__restrict__ b, double *__restrict__ xo) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+// A step on an ELL operator of KT entries a row, one thread per row: all of a row's loads,
+// then all its gathers, are in flight at once. The grid is a multiple of 8: XCD k takes the
+// k-th eighth of the rows, whose operator entries then stay in its L2 from sweep to sweep.
+template <int KT, class Op>
+__global__ __launch_bounds__(256) void k_ell_step(int32_t n, int32_t ld, const int32_t *__restrict__ col,
+                                                  const double *__restrict__ val, const double *__restrict__ x, Op op,
+                                                  double *part) {
+    const uint32_t per = gridDim.x >> 3, blk = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    const int32_t i = blk * blockDim.x + threadIdx.x;
+    double v = 0.0;
+    if (i < n) {
+        const typename Op::In in = op.prepare(i);
+        int32_t j[KT];
+        double a[KT], xs[KT];
+#pragma unroll
+        for (int s = 0; s < KT; ++s) j[s] = col[(size_t)s * ld + i];
+#pragma unroll
+        for (int s = 0; s < KT; ++s) a[s] = val[(size_t)s * ld + i];
+#pragma unroll
+        for (int s = 0; s < KT; ++s) xs[s] = x[j[s]];
+        double acc = 0.0;
+#pragma unroll
+        for (int s = 0; s < KT; ++s) acc += a[s] * xs[s];
+        v = op.apply(i, acc, in);
+    }
+    if constexpr (Op::kReduce) reduce_sq(v, part);
+}
+
+// A lane's share of CSR row .. e1: entries e, e + step, .., three loads and gathers in
+// flight. Past the row's end the last entry is loaded again and counts nothing: a branch
+// around each load would have them wait for each other.
+template <class I, class D, class X>
+__device__ __forceinline__ double csr_share(int32_t e, int32_t e1, int32_t step, I col, D val, X x) {
     double acc = 0.0;
-    for (int32_t s = 0; s < K; ++s) acc += val[(size_t)s * ld + i] * xi[col[(size_t)s * ld + i]];
-    xo[i] = xi[i] + omega * dinv[i] * (b[i] - acc);
+    for (; e < e1; e += 3 * step) {
+        int32_t j[3];
+        double a[3], xs[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) j[u] = col[min(e + u * step, e1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) a[u] = val[min(e + u * step, e1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) xs[u] = x[j[u]];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) acc += e + u * step < e1 ? a[u] * xs[u] : 0.0;
+    }
+    return acc;
 }
 
-// The first damped Jacobi sweep from x = 0: x = omega * dinv * b (the residual is b).
-__global__ __launch_bounds__(256) void k_jacobi_first(int32_t n, double omega, const double *__restrict__ dinv,
-                                                      const double *__restrict__ b, double *__restrict__ x) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = omega * dinv[i] * b[i];
+// A step on a CSR operator, LANES lanes per row.
+template <int LANES, class Op>
+__global__ __launch_bounds__(256) void k_csr_step(int32_t n, const int32_t *__restrict__ ptr,
+                                                  const int32_t *__restrict__ col, const double *__restrict__ val,
+                                                  const double *__restrict__ x, Op op, double *part) {
+    const uint32_t per = gridDim.x >> 3, blk = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    const int32_t i = (int32_t)((blk * blockDim.x + threadIdx.x) / LANES), t = threadIdx.x % LANES;
+    double v = 0.0;
+    if (i < n) {
+        typename Op::In in{};
+        if (t == 0) in = op.prepare(i);
+        double acc = csr_share(ptr[i] + t, ptr[i + 1], LANES, col, val, x);
+#pragma unroll
+        for (int o = LANES / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, LANES);
+        if (t == 0) v = op.apply(i, acc, in);
+    }
+    if constexpr (Op::kReduce) reduce_sq(v, part);
 }
 
-// First Chebyshev sweep: z = D^{-1} r (r = b - A x, or b from a zero iterate),
-// d = z / theta, x += d (x = d from a zero iterate). r may be z.
-__global__ __launch_bounds__(256) void k_cheb_first(int32_t n, double theta, const double *__restrict__ dinv,
-                                                    const double *r, double *z, double *__restrict__ d,
-                                                    double *__restrict__ x, int32_t zero_start) {
+// x += d (a single Chebyshev sweep from a nonzero iterate)
+__global__ __launch_bounds__(256) void k_add(int32_t n, const double *__restrict__ d, double *__restrict__ x) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double zi = dinv[i] * r[i];
-    z[i] = zi;
-    const double di = zi / theta;
-    d[i] = di;
-    x[i] = zero_start ? di : x[i] + di;
-}
-
-// Later Chebyshev sweeps, with w = A d: z -= D^{-1} w, d = c1 d + c2 z, x += d.
-__global__ __launch_bounds__(256) void k_cheb_step(int32_t n, double c1, double c2, const double *__restrict__ dinv,
-                                                   const double *__restrict__ w, double *__restrict__ z,
-                                                   double *__restrict__ d, double *__restrict__ x) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double zi = z[i] - dinv[i] * w[i];
-    z[i] = zi;
-    const double di = c1 * d[i] + c2 * zi;
-    d[i] = di;
-    x[i] += di;
+    if (i < n) x[i] += d[i];
 }
 
 __global__ __launch_bounds__(256) void k_copy(int32_t n, const double *__restrict__ a, double *__restrict__ b) {
@@ -406,11 +551,24 @@ __global__ __launch_bounds__(256) void k_sumsq(int32_t n, const double *__restri
     if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-__global__ __launch_bounds__(64) void k_sumsq_finish(const double *part, double *out) {
+// The nparts partial sums added in a fixed order; the total, then the count of totals so
+// far, go to mapped host memory, which the host watches instead of waiting for a copy.
+__global__ __launch_bounds__(1024) void k_sum_finish(const double *__restrict__ part, int32_t nparts, uint32_t *count,
+                                                     double *htotal, uint32_t *hcount) {
+    __shared__ double red[16];
+    double s = 0.0;
+    for (int32_t b = threadIdx.x; b < nparts; b += 1024) s += part[b];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int b = 0; b < kNormBlocks; ++b) s += part[b];
-        *out = s;
+        double t = red[0];
+        for (int w = 1; w < 16; ++w) t += red[w];
+        const uint32_t c = *count + 1;
+        *count = c;
+        __hip_atomic_store(htotal, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(hcount, c, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -423,144 +581,239 @@ using namespace hec;
 struct hec_amg_level {
     amgs::Csr A, P;                      // host copies (A_l, and P_l for l < L)
     std::vector<int8_t> cf;              // C/F splitting of this level (l < L)
-    std::unique_ptr<hec_matrix_s> dA;    // plain ELL when `fused`, else HEC
-    bool fused = false;
-    std::unique_ptr<hec_matrix_s> dP, dR;
+    std::unique_ptr<hec_matrix_s> dA, dP, dR;  // narrow ELL or CSR each
     DevBuf<double> dinv, x, y, b, r;     // x, y: the iterate and the other buffer of a sweep
     // Chebyshev smoothing: the Gershgorin bound of D^{-1} A, the sweep coefficients for
-    // nu1 and nu2 sweeps, and the product A d (the direction d lives in y, z in r)
+    // nu1 and nu2 sweeps, and the second buffer of the direction (the first is y, z is r)
     double lmax = 0.0, theta = 0.0;
     std::vector<double> c1_pre, c2_pre, c1_post, c2_post;
     DevBuf<double> t;
+};
+
+// What the host watches for the end of a cycle: pinned, mapped, recycled and never freed
+// (freeing pinned memory can synchronise the whole device).
+struct AmgWatch {
+    double total;
+    uint32_t count;
 };
 
 struct hec_amg_s {
     hec_amg_opts opts{};
     std::vector<std::unique_ptr<hec_amg_level>> lev;
     std::unique_ptr<hec_matrix_s> coarse_inv;  // dense inverse of the coarsest level
-    DevBuf<double> part, nrm;
+    DevBuf<double> part;
+    DevBuf<uint32_t> count;                    // totals finished so far
+    uint32_t expect = 0;                       // the same, as the host launched them
+    AmgWatch *watch = nullptr, *dwatch = nullptr;
     hipStream_t hs = nullptr;                  // the handle's stream (the cycle graph replays on it)
     hipEvent_t ev = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    ~hec_amg_s() {
-        if (hs) (void)hipStreamSynchronize(hs);
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
-        lev.clear();
-        coarse_inv.reset();
-        part.release();
-        nrm.release();
-        if (ev) (void)hipEventDestroy(ev);
-        if (hs) (void)hipStreamDestroy(hs);
-    }
+    ~hec_amg_s();
 };
 
 namespace {
 
-std::unique_ptr<hec_matrix_s> upload(const amgs::Csr &M, int32_t width, hipStream_t s) {
-    return make_hec(M.n, M.m, M.p.data(), M.j.data(), M.x.data(), width, 0, s);
+constexpr int kEllNarrow = 8, kEllMax = 20, kEllRows = 16384;
+
+std::mutex g_watch_mu;
+std::vector<AmgWatch *> g_watch_pool;
+
+AmgWatch *take_watch() {
+    {
+        std::lock_guard<std::mutex> lk(g_watch_mu);
+        if (!g_watch_pool.empty()) {
+            AmgWatch *w = g_watch_pool.back();
+            g_watch_pool.pop_back();
+            return w;
+        }
+    }
+    AmgWatch *w = nullptr;
+    HEC_HIP(hipHostMalloc((void **)&w, sizeof(AmgWatch), hipHostMallocMapped | hipHostMallocCoherent));
+    return w;
 }
 
-// y = alpha * M x + beta * z
-void spmv(const hec_matrix_s &M, double alpha, const double *x, double beta, const double *z, double *y,
-          hipStream_t s) {
-    spmv_launch<double, double, double>(M, alpha, x, beta, z, y, s);
+void give_watch(AmgWatch *w) {
+    std::lock_guard<std::mutex> lk(g_watch_mu);
+    g_watch_pool.push_back(w);
 }
 
-void sumsq(hec_amg_s &H, int32_t n, const double *v, hipStream_t s) {
-    k_sumsq<<<kNormBlocks, 256, 0, s>>>(n, v, H.part.get());
+// An operator on the device: plain ELL, a thread per row, where its rows are of about the
+// same length (a slab at most 30% over the entries) and either narrow or, up to 20 entries,
+// many enough to give every SIMD a wavefront; else CSR. Measured per cycle: a 62,500-row
+// level of 18 entries a row as ELL takes the 50^3 Poisson cycle from 160 to 150 us; at
+// 512 rows (a 16^3 system) the same costs 4%.
+std::unique_ptr<hec_matrix_s> upload(const amgs::Csr &M, hipStream_t s) {
+    int32_t width = 0;
+    for (int32_t i = 0; i < M.n; ++i) width = std::max(width, M.p[i + 1] - M.p[i]);
+    const bool ell = width >= 1 && (double)width * M.n <= 1.3 * (double)M.p[M.n] &&
+                     (width <= kEllNarrow || (width <= kEllMax && M.n >= kEllRows));
+    return make_hec(M.n, M.m, M.p.data(), M.j.data(), M.x.data(), ell ? width : 0, 0, s);
+}
+
+// Lanes of a CSR row: about three entries each, so that a row is one round of loads (a
+// 50^3 Poisson cycle with 2, 3, 4, 6 and 8 entries: 166, 160, 163, 163, 168 us).
+int row_lanes(const hec_matrix_s &M) {
+    const double mean = M.n ? (double)M.nnz / M.n : 0.0;
+    int lanes = 2;
+    while (lanes < 64 && 3.0 * lanes < mean) lanes *= 2;
+    return lanes;
+}
+
+// One step of the cycle on operator M (op's vectors, x: the vector multiplied); returns
+// the workgroups launched (partial sums of a reducing op).
+template <class Op>
+unsigned step(const hec_matrix_s &M, const double *x, const Op &op, double *part, hipStream_t s) {
+    if (M.n == 0) return 0;
+    unsigned grid;
+    if (M.K > 0) {
+        grid = (ceil_div(M.n, 256) + 7u) / 8u * 8u;
+#define HEC_AMG_K(KK)                                                                                             \
+    case KK:                                                                                                      \
+        k_ell_step<KK, Op><<<grid, 256, 0, s>>>(M.n, M.ld, M.ell_col.get(), M.ell_val.get(), x, op, part);        \
+        break;
+        switch (M.K) {
+            HEC_AMG_K(1)
+            HEC_AMG_K(2)
+            HEC_AMG_K(3)
+            HEC_AMG_K(4)
+            HEC_AMG_K(5)
+            HEC_AMG_K(6)
+            HEC_AMG_K(7)
+            HEC_AMG_K(8)
+            HEC_AMG_K(9)
+            HEC_AMG_K(10)
+            HEC_AMG_K(11)
+            HEC_AMG_K(12)
+            HEC_AMG_K(13)
+            HEC_AMG_K(14)
+            HEC_AMG_K(15)
+            HEC_AMG_K(16)
+            HEC_AMG_K(17)
+            HEC_AMG_K(18)
+            HEC_AMG_K(19)
+            default:
+                HEC_AMG_K(20)
+        }
+#undef HEC_AMG_K
+    } else {
+        const int lanes = row_lanes(M);
+        grid = (ceil_div((size_t)M.n * lanes, 256) + 7u) / 8u * 8u;
+#define HEC_AMG_L(LL)                                                                                             \
+    case LL:                                                                                                      \
+        k_csr_step<LL, Op><<<grid, 256, 0, s>>>(M.n, M.rem_ptr.get(), M.rem_col.get(), M.rem_val.get(), x, op,    \
+                                                part);                                                            \
+        break;
+        switch (lanes) {
+            HEC_AMG_L(2)
+            HEC_AMG_L(4)
+            HEC_AMG_L(8)
+            HEC_AMG_L(16)
+            HEC_AMG_L(32)
+            default:
+                HEC_AMG_L(64)
+        }
+#undef HEC_AMG_L
+    }
     HEC_CHECK_LAUNCH();
-    k_sumsq_finish<<<1, 64, 0, s>>>(H.part.get(), H.nrm.get());
+    return grid;
+}
+
+// The total of `nparts` partial sums to the host.
+void finish_total(hec_amg_s &H, int32_t nparts, hipStream_t s) {
+    k_sum_finish<<<1, 1024, 0, s>>>(H.part.get(), nparts, H.count.get(), &H.dwatch->total, &H.dwatch->count);
     HEC_CHECK_LAUNCH();
 }
 
-double read_norm(hec_amg_s &H, hipStream_t s) {
-    double h = 0.0;
-    H.nrm.download(&h, 1, s);
-    HEC_HIP(hipStreamSynchronize(s));
-    return std::sqrt(h);
+// Waits for the next total (launched on s) and returns its root. The host watches the
+// count in mapped memory and asks the stream now and then, so that an error ends the wait.
+double wait_norm(hec_amg_s &H, hipStream_t s) {
+    ++H.expect;
+    uint32_t *const count = &H.watch->count;
+    for (uint32_t it = 1; __atomic_load_n(count, __ATOMIC_ACQUIRE) != H.expect; ++it) {
+        __builtin_ia32_pause();
+        if ((it & 0x3FFu) != 0) continue;
+        const hipError_t q = hipStreamQuery(s);
+        if (q == hipErrorNotReady) continue;
+        HEC_HIP(q);
+        HEC_HIP(hipStreamSynchronize(s));
+        if (__atomic_load_n(count, __ATOMIC_ACQUIRE) != H.expect) fail(HEC_ERR_HIP, "an AMG cycle left no residual norm");
+    }
+    return std::sqrt(*(volatile double *)&H.watch->total);
 }
 
 // `sweeps` damped Jacobi sweeps from *cur, alternating between the level's x and y;
-// *cur ends on the buffer that holds the result. zero_start: the iterate is zero,
-// so the first sweep is x = omega D^{-1} b (one elementwise launch, nothing to zero).
-void smooth(hec_amg_level &L, double omega, int sweeps, double *&cur, const double *b, hipStream_t s,
-            bool zero_start = false) {
-    const hec_matrix_s &M = *L.dA;
-    int k = 0;
-    if (zero_start && sweeps > 0) {
-        k_jacobi_first<<<ceil_div(M.n, 256), 256, 0, s>>>(M.n, omega, L.dinv.get(), b, cur);
-        HEC_CHECK_LAUNCH();
-        k = 1;
-    }
-    for (; k < sweeps; ++k) {
-        if (!L.fused) {  // r = b - A x, then x += omega D^{-1} r in place
-            spmv(M, -1.0, cur, 1.0, b, L.r.get(), s);
-            k_jacobi_update<<<ceil_div(M.n, 256), 256, 0, s>>>(M.n, omega, L.dinv.get(), L.r.get(), cur);
-            HEC_CHECK_LAUNCH();
-            continue;
-        }
+// *cur ends on the buffer that holds the result. `done`: sweeps the caller has made.
+void smooth(hec_amg_level &L, double omega, int sweeps, double *&cur, hipStream_t s, int done = 0) {
+    for (int k = done; k < sweeps; ++k) {
         double *nxt = cur == L.x.get() ? L.y.get() : L.x.get();
-        k_jacobi_ell<<<ceil_div(M.n, 256), 256, 0, s>>>(M.n, M.K, M.ld, M.ell_col.get(), M.ell_val.get(),
-                                                       L.dinv.get(), omega, cur, b, nxt);
-        HEC_CHECK_LAUNCH();
+        step(*L.dA, cur, OpJacobi{L.b.get(), L.dinv.get(), cur, nxt, omega}, nullptr, s);
         cur = nxt;
     }
 }
 
-// `sweeps` Chebyshev sweeps on the iterate *cur (which stays where it is; the
-// direction goes to the level's other vector, z to r, A d to t). zero_start: the
-// iterate is zero, so the first residual is b (no product).
+// `sweeps` Chebyshev sweeps on the iterate cur (which stays where it is; the direction
+// alternates between the level's other vector and t, z is r). first_done: the first sweep,
+// from a zero iterate, was made with the restriction (d in the level's other vector).
 void smooth_cheb(hec_amg_level &L, int sweeps, const std::vector<double> &c1, const std::vector<double> &c2,
-                 double *cur, const double *b, hipStream_t s, bool zero_start = false) {
+                 double *cur, hipStream_t s, bool first_done = false) {
     if (sweeps == 0) return;
-    const hec_matrix_s &M = *L.dA;
-    const unsigned g = ceil_div(M.n, 256);
-    double *d = cur == L.x.get() ? L.y.get() : L.x.get();
-    if (!zero_start) spmv(M, -1.0, cur, 1.0, b, L.r.get(), s);  // r = b - A x
-    k_cheb_first<<<g, 256, 0, s>>>(M.n, L.theta, L.dinv.get(), zero_start ? b : L.r.get(), L.r.get(), d, cur,
-                                   zero_start ? 1 : 0);
-    HEC_CHECK_LAUNCH();
+    double *d = cur == L.x.get() ? L.y.get() : L.x.get(), *d2 = L.t.get();
+    bool pending = !first_done;  // x has not taken d yet
+    if (!first_done) step(*L.dA, cur, OpChebFirst{L.b.get(), L.dinv.get(), L.r.get(), d, L.theta}, nullptr, s);
     for (int k = 1; k < sweeps; ++k) {
-        spmv(M, 1.0, d, 0.0, L.t.get(), L.t.get(), s);  // t = A d
-        k_cheb_step<<<g, 256, 0, s>>>(M.n, c1[k - 1], c2[k - 1], L.dinv.get(), L.t.get(), L.r.get(), d, cur);
+        step(*L.dA, d,
+             OpChebStep{L.dinv.get(), d, L.r.get(), d2, cur, c1[k - 1], c2[k - 1], pending ? 1 : 0, k + 1 == sweeps ? 1 : 0},
+             nullptr, s);
+        pending = true;
+        std::swap(d, d2);
+    }
+    if (sweeps == 1 && pending) {
+        k_add<<<ceil_div(L.dA->n, 256), 256, 0, s>>>(L.dA->n, d, cur);
         HEC_CHECK_LAUNCH();
     }
 }
 
-// Alg. 5 from level l (iterate in L.x, right-hand side in L.b); returns the buffer
-// holding the result.
+// Alg. 5 from level l (iterate in L.x, right-hand side in L.b; below level 0 the first
+// sweep, from a zero iterate, is already made); returns the buffer holding the result.
 double *vcycle(hec_amg_s &H, size_t l, hipStream_t s) {
     hec_amg_level &L = *H.lev[l];
     if (l + 1 == H.lev.size()) {
-        spmv(*H.coarse_inv, 1.0, L.b.get(), 0.0, L.b.get(), L.x.get(), s);  // x_L = A_L^{-1} b_L
+        step(*H.coarse_inv, L.b.get(), OpApply{L.x.get()}, nullptr, s);  // x_L = A_L^{-1} b_L
         return L.x.get();
     }
     const hec_amg_opts &o = H.opts;
-    const bool cheb = o.smoother == 1;
+    const bool cheb = o.smoother == 1, begun = l > 0 && o.nu1 > 0;
     double *cur = L.x.get();
     if (cheb)
-        smooth_cheb(L, o.nu1, L.c1_pre, L.c2_pre, cur, L.b.get(), s, l > 0);
+        smooth_cheb(L, o.nu1, L.c1_pre, L.c2_pre, cur, s, begun);
     else
-        smooth(L, o.omega, o.nu1, cur, L.b.get(), s, l > 0);  // below level 0 the iterate starts at zero
-    spmv(*L.dA, -1.0, cur, 1.0, L.b.get(), L.r.get(), s);  // r = b - A x
+        smooth(L, o.omega, o.nu1, cur, s, begun ? 1 : 0);
+    step(*L.dA, cur, OpResidual<false>{L.b.get(), L.r.get()}, nullptr, s);  // r = b - A x
     hec_amg_level &C = *H.lev[l + 1];
-    spmv(*L.dR, 1.0, L.r.get(), 0.0, L.r.get(), C.b.get(), s);  // b_{l+1} = R r
-    if (l + 2 < H.lev.size() && o.nu1 == 0) {  // no pre-smoothing to start from zero with
+    // b_{l+1} = R r; with the coarse level's first sweep from zero unless it has none of its own
+    const bool own = l + 2 < H.lev.size();
+    if (!own || o.nu1 == 0)
+        step(*L.dR, L.r.get(), OpApply{C.b.get()}, nullptr, s);
+    else if (cheb)
+        step(*L.dR, L.r.get(),
+             OpRestrictCheb{C.dinv.get(), C.b.get(), C.r.get(), C.y.get(), C.x.get(), C.theta}, nullptr, s);
+    else
+        step(*L.dR, L.r.get(), OpRestrictJacobi{C.dinv.get(), C.b.get(), C.x.get(), o.omega}, nullptr, s);
+    if (own && o.nu1 == 0) {  // no pre-smoothing to start from zero with
         k_zero<<<ceil_div(C.A.n, 256), 256, 0, s>>>(C.A.n, C.x.get());
         HEC_CHECK_LAUNCH();
     }
     const double *xc = vcycle(H, l + 1, s);
-    spmv(*L.dP, 1.0, xc, 1.0, cur, cur, s);  // x += P x_{l+1}
+    step(*L.dP, xc, OpProlong{cur}, nullptr, s);  // x += P x_{l+1}
     if (cheb)
-        smooth_cheb(L, o.nu2, L.c1_post, L.c2_post, cur, L.b.get(), s);
+        smooth_cheb(L, o.nu2, L.c1_post, L.c2_post, cur, s);
     else
-        smooth(L, o.omega, o.nu2, cur, L.b.get(), s);
+        smooth(L, o.omega, o.nu2, cur, s);
     return cur;
 }
 
-// One cycle on level 0 ending with the iterate back in x, then ||b - A x||^2 into nrm.
+// One cycle on level 0 ending with the iterate back in x, then ||b - A x||^2 to the host.
 void enqueue_cycle(hec_amg_s &H, hipStream_t s) {
     hec_amg_level &L0 = *H.lev[0];
     const int32_t n = L0.A.n;
@@ -569,11 +822,23 @@ void enqueue_cycle(hec_amg_s &H, hipStream_t s) {
         k_copy<<<ceil_div(n, 256), 256, 0, s>>>(n, res, L0.x.get());
         HEC_CHECK_LAUNCH();
     }
-    spmv(*L0.dA, -1.0, L0.x.get(), 1.0, L0.b.get(), L0.r.get(), s);
-    sumsq(H, n, L0.r.get(), s);
+    finish_total(H, (int32_t)step(*L0.dA, L0.x.get(), OpResidual<true>{L0.b.get(), nullptr}, H.part.get(), s), s);
 }
 
 }  // namespace
+
+hec_amg_s::~hec_amg_s() {
+    if (hs) (void)hipStreamSynchronize(hs);
+    if (exec) (void)hipGraphExecDestroy(exec);
+    if (graph) (void)hipGraphDestroy(graph);
+    lev.clear();
+    coarse_inv.reset();
+    part.release();
+    count.release();
+    if (watch) give_watch(watch);
+    if (ev) (void)hipEventDestroy(ev);
+    if (hs) (void)hipStreamDestroy(hs);
+}
 
 extern "C" {
 
@@ -611,10 +876,7 @@ hec_status amg_setup(int32_t n, const int32_t *Ap, const int32_t *Aj, const doub
                 if (dinv[i] == 0.0 || !std::isfinite(dinv[i]))
                     fail(HEC_ERR_ZERO_PIVOT, "AMG level " + std::to_string(H->lev.size()) + ": zero or missing diagonal in row " + std::to_string(i));
             }
-            int32_t width = 0;
-            for (int32_t i = 0; i < nl; ++i) width = std::max(width, L->A.p[i + 1] - L->A.p[i]);
-            L->fused = (double)width * nl <= 1.3 * (double)L->A.p[nl];
-            L->dA = upload(L->A, L->fused ? width : -1, s);
+            L->dA = upload(L->A, s);
             L->dinv.alloc(nl);
             L->dinv.upload(dinv.data(), nl, s);
             L->x.alloc(nl);
@@ -639,8 +901,8 @@ hec_status amg_setup(int32_t n, const int32_t *Ap, const int32_t *Aj, const doub
                     L->P = amgs::direct_interpolation(L->A, Sp, Sj, L->cf, o.theta);
                     amgs::Csr R = amgs::transpose(L->P);
                     Ac = amgs::galerkin(L->A, L->P, R);
-                    L->dP = upload(L->P, -1, s);
-                    L->dR = upload(R, -1, s);
+                    L->dP = upload(L->P, s);
+                    L->dR = upload(R, s);
                 } else {
                     L->cf.clear();
                 }
@@ -658,9 +920,16 @@ hec_status amg_setup(int32_t n, const int32_t *Ap, const int32_t *Aj, const doub
         std::vector<int32_t> ip(nc + 1), ij((size_t)nc * nc);
         for (int32_t i = 0; i <= nc; ++i) ip[i] = i * nc;
         for (size_t e = 0; e < ij.size(); ++e) ij[e] = (int32_t)(e % nc);
-        H->coarse_inv = make_hec(nc, nc, ip.data(), ij.data(), inv.data(), -1, 0, s);
-        H->part.alloc(kNormBlocks);
-        H->nrm.alloc(1);
+        H->coarse_inv = make_hec(nc, nc, ip.data(), ij.data(), inv.data(), 0, 0, s);
+        // partial sums of the residual's norm (a row's lanes are 64 at most) or the right-hand side's
+        H->part.alloc(std::max<size_t>(kNormBlocks, ((size_t)n * (H->lev[0]->dA->K > 0 ? 1 : row_lanes(*H->lev[0]->dA)) +
+                                                     255) / 256 + 8));
+        H->count.alloc(1);
+        const uint32_t none = 0;
+        H->count.upload(&none, 1, s);
+        H->watch = take_watch();
+        H->watch->count = 0;
+        HEC_HIP(hipHostGetDevicePointer((void **)&H->dwatch, H->watch, 0));
         HEC_HIP(hipStreamSynchronize(s));
         HEC_HIP(hipStreamCreateWithFlags(&H->hs, hipStreamNonBlocking));
         HEC_HIP(hipEventCreateWithFlags(&H->ev, hipEventDisableTiming));
@@ -709,13 +978,19 @@ hec_status amg_solve(hec_amg H, const double *b, double *x, int32_t maxit, doubl
         StreamScope scope(s);
         HEC_HIP(hipEventRecord(H->ev, us));  // after the caller's work on b and x
         HEC_HIP(hipStreamWaitEvent(s, H->ev, 0));
+        if (__atomic_load_n(&H->watch->count, __ATOMIC_ACQUIRE) != H->expect) {  // a solve that ended in an error
+            HEC_HIP(hipStreamSynchronize(s));
+            H->expect = __atomic_load_n(&H->watch->count, __ATOMIC_ACQUIRE);
+        }
         hec_amg_level &L0 = *H->lev[0];
         const int32_t n = L0.A.n;
         HEC_HIP(hipMemcpyAsync(L0.b.get(), b, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, s));
         k_zero<<<ceil_div(n, 256), 256, 0, s>>>(n, L0.x.get());
         HEC_CHECK_LAUNCH();
-        sumsq(*H, n, L0.b.get(), s);
-        const double nb = read_norm(*H, s);
+        k_sumsq<<<kNormBlocks, 256, 0, s>>>(n, L0.b.get(), H->part.get());
+        HEC_CHECK_LAUNCH();
+        finish_total(*H, kNormBlocks, s);
+        const double nb = wait_norm(*H, s);
         int32_t it = 0;
         double res = nb > 0.0 ? 1.0 : 0.0;
         hec_status st = HEC_OK;
@@ -740,7 +1015,7 @@ hec_status amg_solve(hec_amg H, const double *b, double *x, int32_t maxit, doubl
                 else
                     enqueue_cycle(*H, s);
                 ++it;
-                res = read_norm(*H, s) / nb;
+                res = wait_norm(*H, s) / nb;
                 if (!std::isfinite(res)) {
                     st = HEC_ERR_BREAKDOWN;
                     break;

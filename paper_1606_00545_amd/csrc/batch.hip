@@ -202,7 +202,7 @@ __device__ __forceinline__ unsigned long long lds_load_bits(const double *p) {
     return __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// One triangle in level order: wavefront w takes chunks w, w + 16, ... (each at
+// One triangle in level order: wavefront w takes every kBW-th chunk from w (each at
 // most 64 rows of one level); a row waits in LDS for each dependency to leave the
 // sentinel. Every dependency lies in an earlier chunk, so the lowest unfinished
 // chunk can always proceed. Lower: dst = L^{-1} src (src in global memory, unit
