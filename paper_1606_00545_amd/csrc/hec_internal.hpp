@@ -264,8 +264,10 @@ struct hec_grid {
     int64_t sa = 0, sb = 0, sc = 0;
     hec::DevBuf<double> coef;  // [claim][step][k][lane]; k = 3 (upper): the reciprocal pivot
     hec::DevBuf<float> coef32;
-    // 3D: two faces of 8 values a step; 2D: one value a step
-    int64_t face_elems() const { return (int64_t)PA * PB * S * (TA == hec::plan::kGT ? 16 : 1); }
+    // 3D: two faces of 8 values for each step of the kernel; 2D: one value a step
+    int64_t face_elems() const {
+        return (int64_t)PA * PB * (TA == hec::plan::kGT ? (S + 3 * hec::plan::kGridLag + 7) / 8 * 8 * 16 : S);
+    }
     int64_t pad_elems() const { return (int64_t)PA * PB * S * 64; }  // positions (claim, step, lane)
 };
 

@@ -636,6 +636,10 @@ inline void make_row_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, con
 constexpr int kGT = 8;                       // tile side on a 3D grid: kGT * kGT = 64 lanes
 constexpr int kGT2 = 64;                     // tile side along a on a 2D grid (64 x 1)
 constexpr int kGT2Min = 16;                  // a 2D grid needs this many columns along a
+// The device kernel of a 3D grid starts each 16 lanes kGridLag steps after the 16 before them
+// (the plan's order has no lag): the value from below, which has to cross between them, may
+// then take the time of 1 + kGridLag steps.
+constexpr int kGridLag = 1;
 constexpr int kGridCoefLower = 3;            // per lane and step: back (c), below (b), left (a)
 constexpr int kGridCoefUpper = 4;            // ... and the reciprocal pivot
 constexpr int kGrid2CoefLower = 2;           // packed for a 2D grid, which has no "below": back, left

@@ -725,58 +725,44 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_trsv_row(int32_t nitems, con
 // Wavefront solve of a triangle on a 3D grid (plan.hpp's GridPlan): one tile of 8 x 8
 // columns per workgroup, tiles claimed in order from a ticket counter (a tile only
 // waits for tiles claimed before it, held by running workgroups).
-//  * Wavefront 0 solves. At step s lane (ma, mb) solves the row at c-index
-//    s - ma - mb of its column; that row's dependencies were solved at step s - 1:
-//    the one behind it along c by the lane itself (a register), the ones along a
-//    and b by lanes (ma - 1, mb) and (ma, mb - 1), or, on the tile's low faces, by
-//    the tiles before it. Each step has a 9 x 9 grid of cells in LDS, a cell per
-//    lane (row mb, column ma; row and column 8 take the high faces' writes)
-//    holding the two values the lane reads: from the left and from below. A lane
-//    writes its result into the left slot of the cell to its right and the below
-//    slot of the cell above in the next step's grid (one LDS instruction), the
-//    face poller fills the slots no lane writes (the left slots of column 0, the
-//    below slots of row 0), and a lane reads its cell in one instruction. A single wavefront issues
-//    at most one instruction every 4 cycles, so the step is kept to a few dozen
-//    instructions: the dependency chain is one LDS round trip and three fused
-//    multiply-adds. Steps run as unrolled blocks of 8 with ring offsets fixed at
-//    compile time and one release per block: about 20 instructions a step where a
-//    whole tile's 64 rows are all valid for the 8 steps (the bulk of a long column),
-//    a few more with validity masks elsewhere (0.13 us a step against 0.19 us for
-//    the general step, which only a column's last, partial block takes).
-//  * Wavefronts 1..kGridPollers poll the tile's incoming face values (8 on the
-//    a-face, 8 on the b-face per step) for a window of the next 4 * HEC_GRID_POLL_R
-//    steps, one lane per value and step, with device-coherent loads until they are
-//    not the sentinel, write each into its step's grid, and raise the count of
-//    leading steps that have all of theirs. (Several pollers would poll the same
-//    window independently; a wider window or more pollers send more device-coherent
-//    loads, and a poll takes longer the more lines it reads: at 128^3 every wider
-//    window or second poller measured slower.)
-//  * The other wavefronts load the coefficients (packed by claim, step and lane, so
-//    every load is a whole line) and the right-hand side of runs of steps into a
-//    ring of LDS slots. They depend on nothing but the ring, so they run ahead.
-//  * The solver stores each result to the output (by row, or in padded tile-step
-//    order for the intermediate of an L-then-U chain) and, on the tile's high
-//    faces, to the face buffer with a device-coherent store, at the index of the
-//    step at which the next tile needs it (the corner lane's value only on the
-//    a-face, where the tile above also reads it).
-// Readiness is the value itself, as in the blocked kernel: the face buffer holds
-// the sentinel before the launch (filled by the previous launch of an L-then-U
-// chain, or by a fill kernel before a lone solve).
-#ifndef HEC_GRID_POLL_R
-#define HEC_GRID_POLL_R 1
-#endif
-#ifndef HEC_GRID_POLLERS
-#define HEC_GRID_POLLERS 1
-#endif
-#ifndef HEC_GRID_POLL_SLEEP
-#define HEC_GRID_POLL_SLEEP 2
-#endif
-constexpr int kGridWaves = 8;    // the solver, the face pollers, then loaders
-constexpr int kGridPollers = HEC_GRID_POLLERS;
-constexpr int kGridLoaders = kGridWaves - 1 - kGridPollers;
-constexpr int kGridBatch = 3;   // consecutive steps a loader has in flight
-constexpr int kGridRing = 32;   // steps in LDS (slots and grids): how far loads run ahead
-static_assert((kGridRing & (kGridRing - 1)) == 0 && kGridRing % 8 == 0 && kGridBatch <= kGridRing, "ring");
+//
+// Lane (ma, mb) of the solver solves its column's row at c-index s - ma - mb - lag at step
+// s, lag = kGridLag for each 16 lanes before it. Its dependencies: the row behind it along c,
+// solved by the lane itself a step earlier (a register); from the left, lane - 1 a step earlier
+// (a DPP shift); from below, lane - 8: in the same 16 lanes a DPP shift too, else, which is
+// what the lag is for, read from LDS a step ahead; on the tile's low faces the values that
+// the tiles before it hand over through global memory.
+//
+// Bound: the path across the tiles, 30 of them for 128 x 128 columns, each 11 to 15 steps and
+// the way of a value from one compute unit to the next; a step is one wavefront's instruction
+// issue. So everything else is kept off the solver, which takes blocks of 4 steps without a
+// branch inside:
+//  * loaders stream the coefficients (packed by claim, step and lane) and the right-hand side
+//    of 8 steps each into registers and, when the ring has room, into a ring of 32 LDS slots;
+//    the solver reads a block's slots while it computes the one before;
+//  * a poller for each low face brings in its 8 values a step, 8 steps at a time, with
+//    device-coherent loads until they are not the sentinel, and counts the leading steps that
+//    have all theirs; the solver looks at the count and the values in one LDS round trip;
+//  * the solver stores the high faces' results for the next tiles at the end of a block (the
+//    corner on the a-face only, where the tile above reads it too); writers take all results
+//    from LDS to the output, by row or in padded tile-step order for the intermediate of an
+//    L-then-U chain; a slot is loaded again once its results were read.
+// Lanes without a row at a step have zero coefficients and a zero right-hand side: they
+// compute zeros (or, once a solution holds infinities, NaN) that reach no row.
+// Readiness of a face value is the value itself, as in the blocked kernel: the face buffer
+// holds the sentinel before the launch (filled by the previous launch of an L-then-U chain,
+// or by a fill kernel before a lone solve).
+// With the neighbours' values passed through LDS cells, a check of the faces and the stores to
+// the output in every step, a step took 131 ns and a tile 2.9 us after the one before; here 78
+// and 2.7. 128^3 L-then-U pair 233 -> 201 us, one triangle 142 -> 104. Measured and not taken
+// (the pair, against the state at the time): blocks of 2 steps (265 : 232) and of 8 (229 : 204,
+// registers), a lag of 2 (250 : 232), 12 wavefronts (281 : 250, registers), a look at the faces
+// in every step (263 : 261), a block's inputs read again after a wait (250 : 232).
+constexpr int kGridWaves = 8;  // the solver, two face pollers, the writers, then loaders
+constexpr int kGridWriters = 2;
+constexpr int kGridLoaders = kGridWaves - 3 - kGridWriters;
+constexpr int kGridRing = 32;  // steps in LDS
+static_assert((kGridRing & (kGridRing - 1)) == 0 && kGridRing % 8 == 0, "ring");
 
 struct GridArgs {
     int32_t NA, NB, NC, PA, PB, S, nclaims;
@@ -786,7 +772,7 @@ struct GridArgs {
 };
 
 // b: right-hand side by row; x: results by row; face: the triangle's face buffer
-// ([claim][face][step][8], sentinel-filled); fill: nfill elements set to the
+// ([claim][face][step][8] in the giving tile's steps, sentinel-filled); fill: nfill elements set to the
 // sentinel for a later solve (may be NULL). bpad / xpad: b / x in padded tile-step
 // order instead, the lower plan's position (claim * S + step) * 64 + lane, which the
 // upper plan visits in reverse (its claim c, step s, lane l is the lower plan's
@@ -802,14 +788,50 @@ struct GridIO {
     int32_t bpad, xpad;
 };
 
-// Dynamic LDS of k_trsv_grid: control words, slots [ring][NCOEF + 1][64], grids
-// [ring][9][9][2] (a cell: the value from the left, the value from below).
-constexpr size_t kGridCtrl = 256;
+// Two values loaded and stored together (in FP64 64 lanes read 16 bytes from LDS in 10 cycles,
+// two 8-byte reads in one ds_read2st64 in 18).
+template <class T>
+struct alignas(2 * sizeof(T)) Two {
+    T x, y;
+};
+
+// Dynamic LDS of k_trsv_grid: control words, slots [ring][SLOT], rows [ring][kGridRow],
+// a row of zeros. A slot: the pairs (back, below) and (left, right-hand side) of the 64 lanes;
+// upper: (back, below), (left, reciprocal pivot), then the right-hand sides. A row: 8 values
+// from the b-face, the 64 results, 8 values from the a-face.
+constexpr int kGridBlock = 4;  // steps of the solver between two looks at what has arrived
+using plan::kGridLag;
+constexpr size_t kGridCtrl = 512;
+constexpr int kGridRow = 80;
+template <bool UPPER>
+constexpr int kGridSlot = UPPER ? 320 : 256;
 template <class T, bool UPPER>
 constexpr size_t grid_lds_bytes() {
-    constexpr int NCOEF = UPPER ? plan::kGridCoefUpper : plan::kGridCoefLower;
-    return kGridCtrl + (size_t)kGridRing * (NCOEF + 1) * 64 * sizeof(T) +
-           (size_t)kGridRing * (plan::kGT + 1) * (plan::kGT + 1) * 2 * sizeof(T);
+    return kGridCtrl + ((size_t)kGridRing * (kGridSlot<UPPER> + kGridRow) + kGridRow) * sizeof(T);
+}
+
+// v of the lane K before in the same 16 lanes; lanes without one: `first`.
+template <int K, class T>
+__device__ __forceinline__ T row_shift(T first, T v) {
+    constexpr int kRowShr = 0x110 + K;  // DPP row_shr:K
+    int f[sizeof(T) / 4], x[sizeof(T) / 4];
+    __builtin_memcpy(f, &first, sizeof(T));
+    __builtin_memcpy(x, &v, sizeof(T));
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) x[k] = __builtin_amdgcn_update_dpp(f[k], x[k], kRowShr, 0xF, 0xF, false);
+    __builtin_memcpy(&v, x, sizeof(T));
+    return v;
+}
+
+// The same, 0 in lanes without one (no register to copy first).
+template <int K, class T>
+__device__ __forceinline__ T row_shift0(T v) {
+    int x[sizeof(T) / 4];
+    __builtin_memcpy(x, &v, sizeof(T));
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) x[k] = __builtin_amdgcn_mov_dpp(x[k], 0x110 + K, 0xF, 0xF, true);
+    __builtin_memcpy(&v, x, sizeof(T));
+    return v;
 }
 
 template <class T, bool UPPER>
@@ -818,9 +840,11 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const
     using U = typename Sentinel<T>::U;
     constexpr U SENT = Sentinel<T>::bits;
     constexpr int NCOEF = UPPER ? plan::kGridCoefUpper : plan::kGridCoefLower;
-    constexpr int TA = plan::kGT, TB = plan::kGT, GG = TA + 1, GA = GG * GG * 2, RM = kGridRing - 1;
+    constexpr int TA = plan::kGT, TB = plan::kGT, RS = kGridRow, RM = kGridRing - 1;
     constexpr int FS = TA;  // face entries per step in each face's buffer
-    constexpr int SLOT = (NCOEF + 1) * 64;  // elements of a slot: [NCOEF][64] coefficients, [64] rhs
+    constexpr int SLOT = kGridSlot<UPPER>;
+    constexpr int NB = kGridBlock, D = kGridLag;
+    static_assert(TA == 8 && TB == 8 && 8 % NB == 0 && D >= 1 && D < NB, "lanes are 8 x 8 columns, blocks 8 steps");
     if (skip && *skip) return;  // uniform: no workgroup touches the counters
     if (io.fill) {
         const T sv = from_bits<T>(SENT);
@@ -830,382 +854,353 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const
     }
     extern __shared__ __align__(16) char gsm[];
     int *const filled = (int *)gsm;          // [ring]: step whose coefficients and rhs a slot holds
-    int *const s_done = filled + kGridRing;  // steps the solver has finished (slots and grids below are free)
-    int *const s_faces = s_done + 1;         // leading steps whose face values are all in their grids
-    int *const s_claim = s_done + 2;
-    int *const s_abort = s_done + 3;
+    int *const s_done = filled + kGridRing;  // steps the solver has finished
+    int *const s_claim = s_done + 1;
+    int *const s_abort = s_done + 2;
+    int *const s_faces = s_done + 4;         // [2]: leading steps whose a-face (b-face) values are all in their rows
+    int *const s_prog = s_done + 6;          // [writers]: all blocks of a writer below this step are read
+    int *const s_none = s_done + 32;         // [64]: written by lanes that have nothing to say
     T *const slots = (T *)(gsm + kGridCtrl);
-    T *const xg = slots + kGridRing * SLOT;  // [ring][9][9][2]: row mb, column ma; left, below
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ma = lane % TA, mb = lane / TA;
+    T *const rows = slots + kGridRing * SLOT;
+    T *const zeros = rows + kGridRing * RS;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // wavefront 4 is on the solver's SIMD: a poller, which computes little
+    const int wave = wid == 4 ? 2 : wid >= 2 && wid < 4 ? wid + 1 : wid;
+    const int ma = lane & 7, mb = lane >> 3;
+    auto lag = [](int l) { return kGridLag * (l >> 4); };
+    auto skew = [&](int l) { return (l & 7) + (l >> 3) + lag(l); };  // lane l's row at step s: c-index s - skew
     if (threadIdx.x == 0) *s_abort = 0;
-    auto give_up = [&]() {
-        __hip_atomic_store(s_abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        record_timeout(G.err);
+    for (int t = threadIdx.x; t < RS; t += blockDim.x) zeros[t] = (T)0;
+    auto lds_load = [](const int *p) {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
+    auto lds_publish = [&](int *p, int v) {  // after this wavefront's LDS accesses above it (they complete in order)
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        if (lane == 0) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     // one more poll of a wait (wave-uniform callers): true when the wait must stop
     auto spun_out = [&](uint32_t &it, bool device_wide) {
         ++it;
         bool stop = it > G.spin;
-        if (!stop && (it & 63) == 0)
-            stop = __hip_atomic_load(s_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0 ||
-                   (device_wide && timed_out(G.err));
+        if (!stop && (it & 63) == 0) stop = lds_load(s_abort) != 0 || (device_wide && timed_out(G.err));
         stop = __builtin_amdgcn_readfirstlane((int)stop) != 0;
-        if (stop) give_up();
+        if (stop) {
+            __hip_atomic_store(s_abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            record_timeout(G.err);
+        }
         return stop;
     };
-    auto lds_load = [](const int *p) {
-        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-    };
-    // waits until the solver has finished step `below` (its slot is free); false: gave up
-    auto wait_done = [&](int below) {
-        uint32_t it = 0;
-        while (lds_load(s_done) <= below) {
-            if (spun_out(it, false)) return false;
-            __builtin_amdgcn_s_sleep(2);
-        }
-        return true;
-    };
+    const int S8 = (G.S + lag(63) + 7) / 8 * 8;  // whole blocks: the last steps hold no row
     for (;;) {
         __syncthreads();
         if (*s_abort) break;  // uniform: read by every thread after the barrier
         if (threadIdx.x == 0) {
             *s_claim = (int)atomicAdd(&sync[0], 1u);
-            *s_done = 0;
-            *s_faces = 0;
+            *s_done = s_faces[0] = s_faces[1] = 0;
         }
         if (threadIdx.x < kGridRing) filled[threadIdx.x] = -1;
-        for (int t = threadIdx.x; t < GA; t += blockDim.x) xg[t] = (T)0;  // step 0: no previous results
+        if ((int)threadIdx.x < kGridWriters) s_prog[threadIdx.x] = 0;
         __syncthreads();
-        const int c = *s_claim;
+        const int c = __builtin_amdgcn_readfirstlane(*s_claim);
         if (c >= G.nclaims) break;
         const int mta = c % G.PA, mtb = c / G.PA;
         const int32_t ta = UPPER ? G.PA - 1 - mta : mta, tb = UPPER ? G.PB - 1 - mtb : mtb;
         // global a and b of the column of lane (ma', mb')
         auto col_a = [&](int m) { return ta * TA + (UPPER ? TA - 1 - m : m); };
         auto col_b = [&](int m) { return tb * TB + (UPPER ? TB - 1 - m : m); };
-        const bool act = col_a(ma) < G.NA && col_b(mb) < G.NB;
-        const int64_t base = (int64_t)col_a(ma) * G.sa + (int64_t)col_b(mb) * G.sb;
-        auto row_at = [&](int32_t mc) { return base + (int64_t)(UPPER ? G.NC - 1 - mc : mc) * G.sc; };
+        // row of lane l's column at its c-index mc, -1: none
+        auto row_of = [&](int l, int32_t mc) -> int64_t {
+            const int32_t ga = col_a(l & 7), gb = col_b(l >> 3);
+            return ga < G.NA && gb < G.NB && (uint32_t)mc < (uint32_t)G.NC
+                       ? ga * G.sa + gb * G.sb + (UPPER ? G.NC - 1 - mc : mc) * G.sc : -1;
+        };
+        // Vectors by row are read and written 8 steps at a time, so that a wavefront's access
+        // falls on few cache lines (at one step the lanes' rows lie on 15 planes): access i of
+        // 8 takes, with columns running along the unit stride, 8 steps of the 8 columns from
+        // 8 i, else a column per lane at the step whose rows lie on plane i (mod 8).
+        const bool along = G.sc == 1;
+        auto acc_col = [&](int i) { return along ? 8 * i + (lane >> 3) : lane; };
+        auto acc_step = [&](int i) { return along ? lane & 7 : (skew(lane) + i) & 7; };
         // this lane's padded tile-step position at step 0, and its change per step
-        const int64_t pq = (int64_t)c * G.S * 64 + lane;
+        const int64_t pq = ((int64_t)c * G.S - lag(lane)) * 64 + lane;
         const int64_t p0 = UPPER ? (int64_t)G.nclaims * G.S * 64 - 1 - pq : pq, pd = UPPER ? -64 : 64;
-
         if (wave == 0) {
             // ---------------- solver
             __builtin_amdgcn_s_setprio(3);
-            const bool has_u = mtb < G.PB - 1;  // a tile above reads the b-face
             // this lane's face store (if any): a-face by mb (the corner too), b-face by ma
-            const bool fst = ma == TA - 1 || (mb == TB - 1 && has_u);
-            T *const fp = io.face + ((int64_t)c * 2 + (ma == TA - 1 ? 0 : 1)) * G.S * 8 +
-                          (ma == TA - 1 ? mb : ma) - (TA - 1) * FS;  // + FS s: the entry of step s
+            const bool fst = (ma == TA - 1 && (mta < G.PA - 1 || (mb == TB - 1 && mtb < G.PB - 1))) ||
+                             (ma != TA - 1 && mb == TB - 1 && mtb < G.PB - 1);
+            T *const fp = io.face + ((int64_t)c * 2 + (ma == TA - 1 ? 0 : 1)) * S8 * FS + (ma == TA - 1 ? mb : ma);
+            int *const done = lane == 0 ? s_done : s_none + lane;
             T xp = (T)0;  // this lane's result of the previous step (0: none)
-            int ready = 0, fready = 0;
+            int ready = 0;   // steps known to be loaded
+            int fready = 0;  // steps known to have their face values
             bool bail = false;
-            // waits until step s is loaded; returns one past the run of loaded steps from s
-            // (8 flags, one per lane, in one LDS round trip)
-            auto scan = [&](int s) -> int {
-                const int u = lane & 7;
+            auto look = [&](int s0) {  // looks at the flags of the ring from step s0, in one LDS round trip
+                const int want = s0 + (lane & RM);
+                const int f = __hip_atomic_load(&filled[want & RM], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                const uint64_t out = __ballot(f != want);
+                ready = max(ready, s0 + (out ? min(__builtin_ctzll(out), kGridRing) : kGridRing));
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            };
+            struct Blk {  // a block's inputs
+                Two<T> c0[NB], c1[NB];
+                T b[NB], fa[NB], nb[D];  // nb: the values from below of the first steps
+            };
+            // step u of the block whose slots start at sl
+            auto load_slot = [&](const T *sl, int u, Blk &H) {
+                H.c0[u] = ((const Two<T> *)(sl + u * SLOT))[lane];
+                H.c1[u] = ((const Two<T> *)(sl + u * SLOT))[64 + lane];
+                if constexpr (UPPER) H.b[u] = sl[u * SLOT + 256 + lane];
+            };
+            // block s0's coefficients and right-hand sides, waited for until they are loaded
+            auto load_slots = [&](int s0, Blk &H) {
                 uint32_t it = 0;
-                for (;;) {
-                    const int want = s + u;
-                    const int f = __hip_atomic_load(&filled[want & RM], __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
-                    const uint64_t m = __ballot(lane < 8 && want < G.S && f == want);
-                    const int ok = __builtin_ctzll(~m);
-                    if (ok > 0) {
-                        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                        return s + ok;
-                    }
-                    if (spun_out(it, false)) {
-                        bail = true;
-                        return s;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-            };
-            auto wait_faces = [&](int s) -> int {  // until step s has its face values
-                uint32_t it = 0;
-                for (;;) {
-                    const int f = lds_load(s_faces);
-                    if (f > s) {
-                        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                        return f;
-                    }
-                    if (spun_out(it, false)) {
-                        bail = true;
-                        return s;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-            };
-            auto ensure = [&](int s) {  // step s loaded and its faces in; false: gave up
-                if (s >= ready) ready = scan(s);
-                if (s >= fready && !bail) fready = wait_faces(s);
-                return !bail;
-            };
-            struct Step {  // one step's coefficients and right-hand side
-                T cv[NCOEF];
-                T bv;
-            };
-            auto load_step = [&](int s, Step &H) {
-                const T *sl = slots + (s & RM) * SLOT + lane;
+                for (look(s0); ready < s0 + NB && !bail; look(s0)) bail = spun_out(it, false);
 #pragma unroll
-                for (int k = 0; k < NCOEF; ++k) H.cv[k] = sl[k * 64];
-                H.bv = sl[NCOEF * 64];
+                for (int u = 0; u < NB; ++u) {
+                    load_slot(slots + (s0 & RM) * SLOT, u, H);
+                    __asm__ volatile("" : "+v"(H.c0[u].x), "+v"(H.c0[u].y), "+v"(H.c1[u].x), "+v"(H.c1[u].y));
+                    if constexpr (UPPER) __asm__ volatile("" : "+v"(H.b[u]));
+                }
             };
-            // the lane's row at step s: c-index s - ma - mb, valid for (unsigned)(s - moff) < ncl
-            const int moff = ma + mb;
-            const uint32_t ncl = act ? (uint32_t)G.NC : 0u;
-            const int64_t dsc = io.xpad ? pd : UPPER ? -G.sc : G.sc;
-            int64_t roff = io.xpad ? p0 : row_at(-moff);  // the output of step 0, advanced by dsc a step
-            const int gl = (mb * GG + ma) * 2;  // this lane's cell
-            // One step: cur holds its inputs; the next step's are read into nxt while it
-            // computes. That read is speculative (unconditional, so that the compiler
-            // counts it exactly when it waits for the neighbours' values) and is repeated
-            // after the wait when the next step was not yet known to be ready. After a
-            // give-up the step still runs (so the two register sets keep one data flow)
-            // but stores nothing.
-            auto step = [&](int s, Step &cur, Step &nxt, bool odd) {
-                const T *g = xg + (s & RM) * GA + gl;
-                const T left = g[0], below = g[1];
-                const bool more = s + 1 < G.S;
-                const bool early = more && s + 1 < ready && s + 1 < fready;
-                load_step(s + 1, nxt);  // (when s + 1 = S: a slot in range, unused)
-                T acc;
-                if constexpr (!UPPER) {  // columns ascending (c along z): back, below, left
-                    acc = cur.bv - cur.cv[0] * xp;
-                    acc -= cur.cv[1] * below;
-                    acc -= cur.cv[2] * left;
-                } else {  // left, below, back; then the reciprocal pivot
-                    acc = cur.bv - cur.cv[2] * left;
-                    acc -= cur.cv[1] * below;
-                    acc -= cur.cv[0] * xp;
-                    acc *= cur.cv[3];
-                }
-                const bool valid = (uint32_t)(s - moff) < ncl;
-                const T xn = valid ? acc : (T)0;
-                T *gn = xg + ((s + 1) & RM) * GA + gl;
-                gn[2] = xn;           // left slot of the cell to the right
-                gn[2 * GG + 1] = xn;  // below slot of the cell above
-                if (valid && !bail) {
-                    io.x[roff] = xn;
-                    if (fst) store_coherent(fp + (int64_t)s * FS, xn);  // the next tile reads it at step s - TA + 1
-                }
-                xp = xn;
-                roff += dsc;
-                // slots and grids up to s are free once read: LDS accesses of one wavefront
-                // complete in order, so the reads issued above are done before this store
-                if (odd || !more) {
+            // block s0's face values, waited for until they are in: the counts are read before the
+            // values, so that a look that finds them needs no second one
+            auto load_faces = [&](int s0, Blk &H) {
+                const T *const row = rows + (s0 & RM) * RS;
+                uint32_t it = 0;
+                for (;;) {
+                    const int f = __hip_atomic_load(s_faces + (lane & 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                    if (lane == 0) __hip_atomic_store(s_done, s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    T b[D];
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) H.fa[u] = row[u * RS + 72 + mb];
+#pragma unroll
+                    for (int u = 0; u < D; ++u) b[u] = row[u * RS + ma];
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) __asm__ volatile("" : "+v"(H.fa[u]));
+#pragma unroll
+                    for (int u = 0; u < D; ++u) {
+                        __asm__ volatile("" : "+v"(b[u]));
+                        H.nb[u] = mb == 0 ? b[u] : H.nb[u];
+                    }
+                    fready = min(__builtin_amdgcn_readlane(f, 0), __builtin_amdgcn_readlane(f, 1));
+                    if (fready >= s0 + NB || bail) break;
+                    bail = spun_out(it, false);
                 }
-                if (more && !early && ensure(s + 1)) load_step(s + 1, nxt);
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
             };
-            // Eight steps s0 .. s0 + 7 (s0 + 8 < S) with the coefficients of all of them and
-            // the next loaded: no load bookkeeping, ring offsets fixed at compile time (the
-            // ring holds whole blocks of 8), one release of the slots at the end; only the
-            // face values are checked step by step, as they arrive. MASKED: lanes whose row
-            // at a step is not valid publish zeros and store nothing; unmasked blocks are
-            // those at which every lane's row is valid (a tile with all 64 columns in the
-            // grid, TA + TB - 2 <= s0 and s0 + 8 <= NC: the bulk of a long column).
-            // On entry H0 holds step s0's coefficients; on exit step s0 + 8's.
-            auto block8 = [&](auto masked, int s0, Step &H0, Step &H1) {
-                constexpr bool MASKED = decltype(masked)::value;
-                T *const gb = xg + (s0 & RM) * GA + gl;
-                T *const gx = xg + ((s0 + 8) & RM) * GA + gl;
-                const T *const sb = slots + (s0 & RM) * SLOT + lane;
-                const T *const sx = slots + ((s0 + 8) & RM) * SLOT + lane;
+            // The steps of block s0, whose inputs are in cur. The next block's are read into nxt,
+            // a step's worth in each step (from slots in range that may not be loaded yet: read
+            // again then). A taken branch costs as much as four instructions of a step, so there
+            // is none here: lanes without a row compute zeros (or, once a solution holds
+            // infinities, NaN) that reach no row and face entries that no tile reads.
+            auto run = [&](int s0, Blk &cur, Blk &nxt) {
+                const int s1 = s0 + NB;
+                if (__builtin_expect(ready < s1 + NB, 0)) look(s1);
+                const bool loaded = ready >= s1 + NB, faced = fready >= s1 + NB;
+                T *const r0 = rows + (s0 & RM) * RS, *const r1 = rows + (s1 & RM) * RS;
+                const T *const sx = slots + (s1 & RM) * SLOT;
+                // the value from below at step s0 + u + D: lanes of the b-face in that step's row,
+                // others in the row of 1 + D steps before it
+                const T *const bm = r0 + (mb == 0 ? D * RS : -RS) + lane;
+                const T *const bp = (s0 == 0 ? zeros : rows + ((s0 - 1) & RM) * RS) + lane;
+                const T *const b0 = mb == 0 ? bm : bp;
+                const T *const be = mb == 0 ? r1 - (NB - D) * RS + lane : bm;
                 T *const fb = fp + (int64_t)s0 * FS;
-                T *xo = io.x + roff;
+                T acc[NB], nb[NB];
+#pragma unroll
+                for (int u = 0; u < D; ++u) nb[u] = cur.nb[u];
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const T bel = (u == 0 ? b0 : u < NB - D ? bm : be)[u * RS];
+                    if (u + D < NB)
+                        nb[u + D < NB ? u + D : 0] = bel;
+                    else
+                        nxt.nb[u + D < NB ? 0 : u + D - NB] = bel;
+                    load_slot(sx, u, nxt);
+                    nxt.fa[u] = r1[u * RS + 72 + mb];
+                    T left = row_shift0<1>(xp);
+                    __asm__ volatile("" : "+v"(left));  // (every lane shifts: not under the condition below)
+                    left = ma == 0 ? cur.fa[u] : left;
+                    const T below = row_shift<8>(nb[u], xp);
+                    T v;
+                    if constexpr (!UPPER) {  // columns ascending (c along z): back, below, left
+                        v = cur.c1[u].y - cur.c0[u].x * xp;
+                        v -= cur.c0[u].y * below;
+                        v -= cur.c1[u].x * left;
+                    } else {  // left, below, back; then the reciprocal pivot
+                        v = cur.b[u] - cur.c1[u].x * left;
+                        v -= cur.c0[u].y * below;
+                        v -= cur.c0[u].x * xp;
+                        v *= cur.c1[u].y;
+                    }
+                    (r0 + u * RS)[8 + lane] = v;
+                    acc[u] = xp = v;
+                }
+                // an arithmetic result is never the signalling-NaN sentinel (IEEE mode quiets
+                // NaN operands), so no check is needed before publishing it
+                if (fst) {
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) {
+                        U bits;
+                        __builtin_memcpy(&bits, &acc[u], sizeof(T));
+                        __hip_atomic_store((U *)(fb + u * FS), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                __hip_atomic_store(done, s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (__builtin_expect(!loaded && s1 < S8, 0)) load_slots(s1, nxt);  // (after a give-up: never used)
+                if (__builtin_expect(!faced, 1)) {
+                    if (s1 < S8) load_faces(s1, nxt);
+                }
+            };
+            Blk h0, h1;
+#pragma unroll
+            for (int u = 0; u < D; ++u) h0.nb[u] = (T)0;
+            load_slots(0, h0);
+            load_faces(0, h0);
+            for (int s0 = 0; s0 < S8 && !bail; s0 += 2 * NB) {
+                run(s0, h0, h1);
+                if (s0 + NB < S8 && !bail) run(s0 + NB, h1, h0);
+            }
+            __builtin_amdgcn_s_setprio(0);
+        } else if (wave <= 2) {
+            // ---------------- face pollers, one per face: lane 8 q + j polls entry j of step w + q;
+            // a value goes into the step's row once, when it has arrived and the solver is done
+            // with the row's previous use; the window moves on by the leading steps that have
+            // all theirs
+            const bool on_a = wave == 1;
+            const int q = lane >> 3, j = lane & 7, lg = on_a ? lag(8 * j) : 0;
+            // a-face entry j: a-face of the tile before along a; b-face entry j: b-face of the
+            // tile below, its corner (j = 7) on that tile's a-face
+            // (the faces are in the order of the giving tile's steps)
+            const T *const fsrc = io.face + j + (on_a       ? ((int64_t)(c - 1) * 2 + 0) * S8 * FS + (TA - 1) * FS
+                                                 : ((int64_t)(c - G.PA) * 2 + (j == TA - 1 ? 0 : 1)) * S8 * FS +
+                                                       (TB - 1 + lag(63)) * FS);
+            T *const gp = rows + (on_a ? 72 + j : j);
+            const bool has = on_a ? mta > 0 && col_b(j) < G.NB : mtb > 0 && col_a(j) < G.NA;
+            int w = 0;
+            if ((on_a ? mta : mtb) == 0) {  // no tile before it on this side: zeros, and nothing to poll
+                for (int r = q; r < kGridRing; r += 8) gp[r * RS] = (T)0;
+                lds_publish(s_faces + wave - 1, INT_MAX);
+                w = S8;
+            }
+            bool wr = false;  // this lane's value of step w + q is in its row
+            uint32_t it = 0;
+            int dn = 0;  // steps the solver is known to have finished
+            while (w < S8) {
+                const int st = w + q;
+                if (w + 8 > dn + kGridRing) dn = lds_load(s_done);
+                const bool can = !wr && st < S8 && st < dn + kGridRing;
+                const bool need = can && has && (uint32_t)(st - lg - j) < (uint32_t)G.NC;
+                const U v = need ? load_coherent(fsrc + (int64_t)st * FS) : (U)0;
+                if (can && (!need || v != SENT)) {
+                    gp[(st & RM) * RS] = need ? from_bits<T>(v) : (T)0;
+                    wr = true;
+                }
+                uint64_t t = __ballot(wr || st >= S8);  // bit 8 q ends up set when all of step w + q is in
+                t &= t >> 4;
+                t &= t >> 2;
+                t &= t >> 1;
+                t = ~t & 0x0101010101010101ull;
+                const int k = t ? __builtin_ctzll(t) >> 3 : 8;  // leading steps of the window with all their values
+                if (k == 0) {
+                    if (spun_out(it, true)) break;
+                    continue;
+                }
+                it = 0;
+                lds_publish(s_faces + wave - 1, w + k);
+                const int from = lane + 8 * k;  // lane l takes over lane l + 8 k's entry
+                const int nw = __shfl((int)wr, from < 64 ? from : lane);
+                wr = from < 64 && nw != 0;
+                w += k;
+            }
+        } else if (wave < 3 + kGridWriters) {
+            // ---------------- writers: blocks of 8 steps in turn
+            const int wi = wave - 3;
+            for (int s0 = 8 * wi; s0 < S8; s0 += 8 * kGridWriters) {
+                uint32_t it = 0;
+                bool quit = false;
+                while (lds_load(s_done) < s0 + 8) {
+                    if (spun_out(it, false)) {
+                        quit = true;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                if (quit) break;
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                auto result = [&](int l, int u) {
+                    return rows[((s0 + u) & RM) * RS + 8 + l];
+                };
+                T v[8];
+                if (io.xpad) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = result(lane, u);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (row_of(lane, s0 + u - skew(lane)) >= 0) io.x[p0 + (s0 + u) * pd] = v[u];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = result(acc_col(i), acc_step(i));
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int64_t row = row_of(acc_col(i), s0 + acc_step(i) - skew(acc_col(i)));
+                        if (row >= 0) io.x[row] = v[i];
+                    }
+                }
+                lds_publish(s_prog + wi, s0 + 8 * kGridWriters);
+            }
+            lds_publish(s_prog + wi, INT_MAX);
+        } else {
+            // ---------------- loaders: blocks of 8 consecutive steps in turn, each in flight at
+            // once; a block waits in registers until its slots' previous results were read, so
+            // that what is in flight does not end with the ring
+            for (int s0 = (wave - 3 - kGridWriters) * 8; s0 < S8; s0 += kGridLoaders * 8) {
+                T cv[8][NCOEF], bv[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int s = s0 + u;
-                    if (s >= fready) {
-                        fready = wait_faces(s);
-                        if (bail) break;
-                    }
-                    Step &cur = (u & 1) ? H1 : H0;
-                    Step &nxt = (u & 1) ? H0 : H1;
-                    const T *g = gb + u * GA;
-                    const T left = g[0], below = g[1];
-                    const T *sl = u < 7 ? sb + (u + 1) * SLOT : sx;
+                    const int o = s - lag(lane);  // the packed order has no lag
+                    const bool in = (uint32_t)o < (uint32_t)G.S;
+                    const T *cp = coef + ((int64_t)c * G.S + (in ? o : 0)) * NCOEF * 64 + lane;
 #pragma unroll
-                    for (int k = 0; k < NCOEF; ++k) nxt.cv[k] = sl[k * 64];
-                    nxt.bv = sl[NCOEF * 64];
-                    T acc;
-                    if constexpr (!UPPER) {
-                        acc = cur.bv - cur.cv[0] * xp;
-                        acc -= cur.cv[1] * below;
-                        acc -= cur.cv[2] * left;
-                    } else {
-                        acc = cur.bv - cur.cv[2] * left;
-                        acc -= cur.cv[1] * below;
-                        acc -= cur.cv[0] * xp;
-                        acc *= cur.cv[3];
-                    }
-                    const bool valid = !MASKED || (uint32_t)(s - moff) < ncl;
-                    if constexpr (MASKED) acc = valid ? acc : (T)0;
-                    T *gn = u < 7 ? gb + (u + 1) * GA : gx;
-                    gn[2] = acc;
-                    gn[2 * GG + 1] = acc;
-                    if (valid) *xo = acc;
-                    xo += dsc;
-                    // an arithmetic result is never the signalling-NaN sentinel (IEEE mode
-                    // quiets NaN operands), so no check is needed before publishing it
-                    if (valid && fst) {
-                        U bits;
-                        __builtin_memcpy(&bits, &acc, sizeof(T));
-                        __hip_atomic_store((U *)(fb + u * FS), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    xp = acc;
+                    for (int k = 0; k < NCOEF; ++k) cv[u][k] = in ? cp[k * 64] : (T)0;
+                    const int64_t at = io.bpad ? row_of(lane, s - skew(lane)) >= 0 ? p0 + s * pd : -1
+                                               : row_of(acc_col(u), s0 + acc_step(u) - skew(acc_col(u)));
+                    bv[u] = at >= 0 ? io.b[at] : (T)0;
                 }
-                roff += 8 * dsc;
-                if (!bail) {
-                    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                    if (lane == 0) __hip_atomic_store(s_done, s0 + 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                uint32_t it = 0;
+                bool quit = false;
+                for (;;) {
+                    int m = INT_MAX;
+#pragma unroll
+                    for (int k = 0; k < kGridWriters; ++k) m = min(m, lds_load(s_prog + k));
+                    if (m >= s0 + 8 - kGridRing) break;
+                    if (spun_out(it, false)) {
+                        quit = true;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(2);
                 }
-            };
-            const bool full = __ballot(act) == ~0ull;
-            Step h0, h1;
-            if (ensure(0)) load_step(0, h0);
-            for (int s0 = 0; s0 < G.S && !bail; s0 += 8) {
-                const bool whole = full && s0 >= TA + TB - 2 && s0 + 8 <= G.NC;
-                if (whole || s0 + 8 < G.S) {
-                    while (ready <= s0 + 8 && !bail) ready = scan(ready);
-                    if (bail) break;
-                    if (whole)
-                        block8(std::integral_constant<bool, false>{}, s0, h0, h1);
+                if (quit) break;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    T *const sl = slots + ((s0 + u) & RM) * SLOT;
+                    ((Two<T> *)sl)[lane] = Two<T>{cv[u][0], cv[u][1]};
+                    if constexpr (UPPER)
+                        ((Two<T> *)sl)[64 + lane] = Two<T>{cv[u][2], cv[u][3]};
                     else
-                        block8(std::integral_constant<bool, true>{}, s0, h0, h1);
-                } else {  // the last, partial block
-                    for (int s = s0; s < min(s0 + 8, G.S) && !bail; s += 2) {
-                        if (s >= ready || s >= fready) ensure(s);  // after a block: step s's faces
-                        step(s, h0, h1, false);
-                        if (s + 1 < G.S) step(s + 1, h1, h0, true);
-                    }
-                }
-            }
-            __builtin_amdgcn_s_setprio(0);
-        } else if (wave <= kGridPollers) {
-            // ---------------- face pollers: a window of 4R steps from w, step w + q + 4r in
-            // lane 16q + i for r < R; i < 8: a-face entry i (lane (0, i)), i >= 8:
-            // b-face entry i - 8 (lane (i - 8, 0)). A value goes into its step's grid once,
-            // when it has arrived and the solver is done with the grid's previous step; the
-            // window moves on by whole groups of 4 steps, and the count of leading steps
-            // with all their values is published as it grows.
-            constexpr int R = HEC_GRID_POLL_R;
-            const int q = lane >> 4, i = lane & 15, j = i & 7;
-            const bool on_a = i < 8;
-            const bool has = on_a ? mta > 0 && col_b(j) < G.NB : mtb > 0 && col_a(j) < G.NA;
-            // a-face entry j: a-face of the tile before along a; b-face entry j: b-face of the
-            // tile below, its corner (j = 7) on that tile's a-face
-            const T *const fsrc = !has              ? io.face  // (not read)
-                                  : on_a            ? io.face + ((int64_t)(c - 1) * 2 + 0) * G.S * 8 + j
-                                  : j == TA - 1     ? io.face + ((int64_t)(c - G.PA) * 2 + 0) * G.S * 8 + j
-                                                    : io.face + ((int64_t)(c - G.PA) * 2 + 1) * G.S * 8 + j;
-            // a-face: left slot of lane (0, j)'s cell; b-face: below slot of lane (j, 0)'s cell
-            const int gpos = on_a ? j * GG * 2 : j * 2 + 1;
-            int w = 0, pub = 0;
-            bool wr[R] = {};  // this lane's value of step w + q + 4r is in its grid
-            uint32_t it = 0;
-            while (pub < G.S) {
-                const int dn = lds_load(s_done);
-                U v[R];
-                bool need[R], can[R];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {  // all loads first, then one wait
-                    const int st = w + q + 4 * r;
-                    can[r] = !wr[r] && st < G.S && st < dn + kGridRing;
-                    need[r] = can[r] && has && st - j >= 0 && st - j < G.NC;
-                    v[r] = need[r] ? load_coherent(fsrc + (int64_t)st * 8) : (U)0;
-                }
-                uint64_t okm[R];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int st = w + q + 4 * r;
-                    if (can[r] && (!need[r] || v[r] != SENT)) {
-                        xg[(st & RM) * GA + gpos] = need[r] ? from_bits<T>(v[r]) : (T)0;
-                        wr[r] = true;
-                    }
-                    okm[r] = __ballot(wr[r] || st >= G.S);
-                }
-                int k = 0;  // leading steps of the window with all their values
-                if constexpr (R == 1) {
-                    uint64_t t = okm[0];  // bit 16 q ends up set when all 16 lanes of step w + q are in
-                    t &= t >> 8;
-                    t &= t >> 4;
-                    t &= t >> 2;
-                    t &= t >> 1;
-                    const uint32_t g = (uint32_t)((t & 1) | ((t >> 15) & 2) | ((t >> 30) & 4) | ((t >> 45) & 8));
-                    k = __builtin_ctz(~g);
-                } else {
-                    bool gap = false;
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int qq = 0; qq < 4; ++qq) {
-                            gap = gap || ((okm[r] >> (16 * qq)) & 0xFFFFull) != 0xFFFFull;
-                            k += gap ? 0 : 1;
-                        }
-                }
-                if (w + k > pub) {
-                    pub = min(w + k, G.S);
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // after this wave's writes
-                    if (lane == 0) {  // one poller: its count only grows; several: the largest
-                        if constexpr (kGridPollers == 1)
-                            __hip_atomic_store(s_faces, pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        else
-                            __hip_atomic_fetch_max(s_faces, pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                    it = 0;
-                } else {
-                    if (spun_out(it, true)) break;
-                    __builtin_amdgcn_s_sleep(HEC_GRID_POLL_SLEEP);
-                }
-                const int gsh = k >> 2;  // whole groups done: the window moves on
-                if (gsh > 0) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        bool nw = false;
-#pragma unroll
-                        for (int u = 1; u < R; ++u) nw = u == gsh && r + u < R ? wr[r + u] : nw;
-                        wr[r] = nw;
-                    }
-                    w += 4 * gsh;
-                }
-            }
-        } else {
-            // ---------------- loaders: wavefront 1 + kGridPollers + l takes runs of kGridBatch consecutive
-            // steps, l * kGridBatch + i * L * kGridBatch (L loaders), each run in flight at
-            // once; a run only waits for its own slots, so loads run up to the ring's
-            // depth ahead of the solver
-            constexpr int NL = kGridLoaders, B = kGridBatch;
-            for (int s0 = (wave - 1 - kGridPollers) * B; s0 < G.S; s0 += NL * B) {
-                if (!wait_done(min(s0 + B, G.S) - 1 - kGridRing)) break;
-                T cv[B][NCOEF], bv[B];
-#pragma unroll
-                for (int u = 0; u < B; ++u) {
-                    const int s = s0 + u;
-                    const bool in = s < G.S;
-                    const T *cp = coef + ((int64_t)c * G.S + (in ? s : s0)) * NCOEF * 64 + lane;
-#pragma unroll
-                    for (int k = 0; k < NCOEF; ++k) cv[u][k] = cp[k * 64];
-                    const int32_t mc = s - ma - mb;
-                    bv[u] = in && act && mc >= 0 && mc < G.NC ? io.b[io.bpad ? p0 + s * pd : row_at(mc)] : (T)0;
+                        sl[128 + 2 * lane] = cv[u][2];
                 }
 #pragma unroll
-                for (int u = 0; u < B; ++u) {
-                    const int s = s0 + u;
-                    if (s < G.S) {
-                        T *sl = slots + (s & RM) * SLOT + lane;
-#pragma unroll
-                        for (int k = 0; k < NCOEF; ++k) sl[k * 64] = cv[u][k];
-                        sl[NCOEF * 64] = bv[u];
-                    }
+                for (int u = 0; u < 8; ++u) {
+                    const int st = io.bpad ? u : acc_step(u), l = io.bpad ? lane : acc_col(u);
+                    slots[((s0 + st) & RM) * SLOT + (UPPER ? 256 + l : 129 + 2 * l)] = bv[u];
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                if (lane < B && s0 + lane < G.S)
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if (lane < 8)
                     __hip_atomic_store(&filled[(s0 + lane) & RM], s0 + lane, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -1256,8 +1251,7 @@ constexpr size_t grid2_lds_bytes() {
     return kG2Ctrl + (size_t)kG2Ring * sizeof(T) + (size_t)kG2Ring * (NC2 * 64 + kG2Row) * sizeof(T);
 }
 
-// The coefficients back and left of a row, loaded and stored together (16 bytes in FP64:
-// 64 lanes read them from LDS in 10 cycles, two 8-byte reads in one ds_read2st64 in 18).
+// The coefficients back and left of a row, loaded and stored together.
 template <class T>
 struct alignas(2 * sizeof(T)) Pair {
     T back, left;
@@ -1322,7 +1316,9 @@ __global__ __launch_bounds__(64 * kG2Waves) void k_trsv_grid2(GridArgs G, const 
     Pair<T> *const cpr = (Pair<T> *)(fring + kG2Ring);   // [ring][64] coefficients
     T *const rhs = (T *)(cpr + kG2Ring * 64);            // [ring][kG2Row] right-hand side, then result
     T *const rpv = rhs + kG2Ring * kG2Row;               // [ring][64] reciprocal pivot (upper)
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // wavefront 4 is on the solver's SIMD: the poller, which computes little
+    const int wave = wid == 4 ? 1 : wid >= 1 && wid < 4 ? wid + 1 : wid;
     if (threadIdx.x == 0) *s_abort = 0;
     auto lds_load = [](const int *p) {
         return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
@@ -1356,7 +1352,7 @@ __global__ __launch_bounds__(64 * kG2Waves) void k_trsv_grid2(GridArgs G, const 
         if ((int)threadIdx.x < kG2Writers) s_prog[threadIdx.x] = 0;
         if (threadIdx.x < kG2Ring) fring[threadIdx.x] = (T)0;  // (a tile without one before it: no poller writes)
         __syncthreads();
-        const int c = *s_claim;
+        const int c = __builtin_amdgcn_readfirstlane(*s_claim);
         if (c >= G.nclaims) break;
         const int32_t ta = UPPER ? G.PA - 1 - c : c;
         // row of column l of the tile at its c-index mc, -1: none
