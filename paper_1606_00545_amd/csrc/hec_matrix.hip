@@ -10,6 +10,7 @@
 #include <memory>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "hec_internal.hpp"
 
@@ -201,21 +202,26 @@ __global__ __launch_bounds__(256) void k_spmv_ell(int32_t n, int32_t Kd, int32_t
     }
     const int32_t K = Kd;
     int32_t s = 0;
-    for (; s + 4 <= K; s += 4) {
-        int32_t j0 = __builtin_nontemporal_load(c + (size_t)(s + 0) * ld);
-        int32_t j1 = __builtin_nontemporal_load(c + (size_t)(s + 1) * ld);
-        int32_t j2 = __builtin_nontemporal_load(c + (size_t)(s + 2) * ld);
-        int32_t j3 = __builtin_nontemporal_load(c + (size_t)(s + 3) * ld);
-        VT a0 = __builtin_nontemporal_load(v + (size_t)(s + 0) * ld);
-        VT a1 = __builtin_nontemporal_load(v + (size_t)(s + 1) * ld);
-        VT a2 = __builtin_nontemporal_load(v + (size_t)(s + 2) * ld);
-        VT a3 = __builtin_nontemporal_load(v + (size_t)(s + 3) * ld);
-        XT x0 = x[j0], x1 = x[j1], x2 = x[j2], x3 = x[j3];
-        acc += (AT)a0 * (AT)x0;
-        acc += (AT)a1 * (AT)x1;
-        acc += (AT)a2 * (AT)x2;
-        acc += (AT)a3 * (AT)x3;
-    }
+    auto batch = [&](auto uc) {  // U slots: all loads, then all gathers in flight
+        constexpr int U = decltype(uc)::value;
+        for (; s + U <= K; s += U) {
+            int32_t j[U];
+            VT a[U];
+            XT xs[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) j[u] = __builtin_nontemporal_load(c + (size_t)(s + u) * ld);
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[u] = __builtin_nontemporal_load(v + (size_t)(s + u) * ld);
+#pragma unroll
+            for (int u = 0; u < U; ++u) xs[u] = x[j[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc += (AT)a[u] * (AT)xs[u];
+        }
+    };
+    // 10 at a time: the default width, 20, takes two rounds (300,000 power-law rows, FP64: 42.7 us
+    // with 4 in flight, 42.6, 41.7, 40.3 and 41.7 with 5, 8, 10 and 20)
+    batch(std::integral_constant<int, 10>());
+    batch(std::integral_constant<int, 4>());
     for (; s < K; ++s) {
         int32_t j = __builtin_nontemporal_load(c + (size_t)s * ld);
         VT a = __builtin_nontemporal_load(v + (size_t)s * ld);
