@@ -34,7 +34,8 @@ namespace hec {
 namespace {
 
 constexpr int kBT = 512;          // threads per system (256 registers each: deep loads instead of more wavefronts)
-constexpr int kBW = kBT / 64;     // wavefronts per system
+constexpr int kBW = kBatchWaves;  // wavefronts per system
+static_assert(kBW == kBT / 64, "wavefronts of a workgroup");
 constexpr int kBMaxM = 32;        // largest restart length
 constexpr int kBRedStride = 33;   // per-wavefront partial sums in LDS
 
@@ -85,6 +86,8 @@ struct BatchSys {
     int64_t sa, sb, sc;
     const GDouble *coefL, *coefU;
     const GFloat *coefL32, *coefU32;
+    const GDouble *gpiv;  // the upper plan's pivots, a value per step and lane
+    const GFloat *gpiv32;
     const GDouble *b;
     GDouble *x;
     GDouble *ws;  // (2m + 3) * n doubles: V (m+1), Z (m), r, w
@@ -282,6 +285,9 @@ template <> __device__ __forceinline__ const GDouble *gcoef<double>(const HEC_CO
 template <> __device__ __forceinline__ const GFloat *gcoef<float>(const HEC_CONST BatchSys &S, bool up) {
     return up ? S.coefU32 : S.coefL32;
 }
+template <class VT> __device__ __forceinline__ const Global<VT> *gpiv(const HEC_CONST BatchSys &S);
+template <> __device__ __forceinline__ const GDouble *gpiv<double>(const HEC_CONST BatchSys &S) { return S.gpiv; }
+template <> __device__ __forceinline__ const GFloat *gpiv<float>(const HEC_CONST BatchSys &S) { return S.gpiv32; }
 
 // One triangle of a factor with wavefront plans, in place on y (LDS, by row): level by
 // level of the grid, a lane per column, wavefront w holding the columns of tiles (claims)
@@ -292,7 +298,11 @@ template <> __device__ __forceinline__ const GFloat *gcoef<float>(const HEC_CONS
 // LDS round trip and three fused multiply-adds each; the coefficients, which come from L2
 // or beyond, are loaded 12 (8 in 3D) levels ahead, shared among NT tiles (4 ahead, a level
 // took 0.4 us). In level order with polled dependencies a 63 x 63 system's two triangles
-// took 142 us and a 16^3 system's 59; now 27 and 28.
+// took 142 us and a 16^3 system's 59; now 33 and 29. A row of U is divided by its pivot in FP64,
+// as in level order (FP32 pivots too): a product with the packed reciprocal, in FP32 an FP32
+// number, has up to 2^-24 more error a row; 48 systems of 1,000 to 4,200 rows took 5.3 ms
+// with it and take 5.7. The quotient from a reciprocal of its own and one correction by the
+// remainder, with the guards that makes it the same for every operand: 6.0 ms.
 // Not inlined: with its registers allocated apart from the solver's, the levels ahead stay
 // in registers (a spill reload in the loop waits for every load in flight).
 template <class VT, bool UPPER, bool FLAT, bool MANY, int NT>
@@ -305,6 +315,7 @@ __device__ __attribute__((noinline)) void b_grid(const HEC_CONST BatchSys *sys, 
     done = uniform_lds(done);
     const uint32_t spin = __builtin_amdgcn_readfirstlane(spin_v);
     const Global<VT> *const coef = gcoef<VT>(S, UPPER);
+    const Global<VT> *const piv = gpiv<VT>(S);
     constexpr int TA = FLAT ? plan::kGT2 : plan::kGT, TB = 64 / TA, U = (FLAT ? 12 : 8) / NT, LEFT = FLAT ? 1 : 2;
     constexpr int NC = FLAT ? (UPPER ? plan::kGrid2CoefUpper : plan::kGrid2CoefLower)
                             : (UPPER ? plan::kGridCoefUpper : plan::kGridCoefLower);
@@ -325,14 +336,14 @@ __device__ __attribute__((noinline)) void b_grid(const HEC_CONST BatchSys *sys, 
     const int sc = UPPER ? -(int)S.sc : (int)S.sc;
     const int da = UPPER ? (int)S.sa : -(int)S.sa, db = UPPER ? (int)S.sb : -(int)S.sb;
     struct Lev {
-        VT cv[NC];  // back, (below,) left, (reciprocal pivot)
+        VT cv[NC];  // back, (below,) left, (pivot)
         double b;
     };
     struct Tile {
         int first, ncl, row0;  // level of this lane's first row; its rows; where the first is
         int oa, ob;            // from a row to its left and below neighbour (0: none, whose coefficient is 0 ..
         bool has_a, has_b;     // .. and whose value is taken as 0)
-        const Global<VT> *base;  // the tile's coefficients (uniform)
+        const Global<VT> *base, *pbase;  // the tile's coefficients and pivots (uniform)
         int t0;                // level t is the tile's step t + t0
         double xp;             // this lane's result of the level before
         Lev ring[U];
@@ -342,14 +353,14 @@ __device__ __attribute__((noinline)) void b_grid(const HEC_CONST BatchSys *sys, 
     auto load = [&](const Tile &T, int t, Lev &H) {
         const int st = min(max(t + T.t0, 0), S.S - 1);
         const Global<VT> *cp = T.base + (size_t)st * (64 * NC);
-        if constexpr (FLAT) {  // the pair (back, left) of the lane, then the reciprocals
+        if constexpr (FLAT) {  // the pair (back, left) of the lane
             H.cv[0] = cp[2 * lane];
             H.cv[1] = cp[2 * lane + 1];
-            if constexpr (UPPER) H.cv[2] = cp[128 + lane];
         } else {
 #pragma unroll
-            for (int k = 0; k < NC; ++k) H.cv[k] = cp[k * 64 + lane];
+            for (int k = 0; k <= LEFT; ++k) H.cv[k] = cp[k * 64 + lane];
         }
+        if constexpr (UPPER) H.cv[LEFT + 1] = T.pbase[(size_t)st * 64 + lane];
         const int idx = t - T.first;
         H.b = y[(unsigned)idx < (unsigned)T.ncl ? T.row0 + idx * sc : 0];
     };
@@ -377,7 +388,7 @@ __device__ __attribute__((noinline)) void b_grid(const HEC_CONST BatchSys *sys, 
             acc = H.b - (double)H.cv[LEFT] * left;
             if constexpr (!FLAT) acc -= (double)H.cv[1] * below;
             acc -= (double)H.cv[0] * T.xp;
-            acc *= (double)H.cv[LEFT + 1];
+            acc = acc / (double)H.cv[LEFT + 1];
         }
         if (ok) y[row] = acc;
         T.xp = ok ? acc : 0.0;
@@ -399,6 +410,7 @@ __device__ __attribute__((noinline)) void b_grid(const HEC_CONST BatchSys *sys, 
         T[k].oa = T[k].has_a ? da : 0;
         T[k].ob = T[k].has_b ? db : 0;
         T[k].base = coef + (size_t)c * S.S * (64 * NC);
+        T[k].pbase = piv + (size_t)c * S.S * 64;
         T[k].xp = 0.0;
     }
     // the loads of the first levels in the order the loop issues them: where the two orders
@@ -854,7 +866,7 @@ hec_status gmres_solve_batched(hec_batch B, int32_t count, const hec_matrix *A, 
             S.nchU = fu.nchunks;
             const hec_grid &gl = l->lower.grid, &gu = l->upper.grid;
             S.ntiles = 0;
-            if (gl.on && gu.on && gl.PA * gl.PB <= (gl.TA == plan::kGT ? 2 : 1) * kBW) {  // (b_grid: NT)
+            if (gl.on && batch_takes_grid(gu)) {
                 S.ntiles = gl.PA * gl.PB;
                 S.TA = gl.TA;
                 S.NA = gl.NA;
@@ -870,6 +882,8 @@ hec_status gmres_solve_batched(hec_batch B, int32_t count, const hec_matrix *A, 
                 S.coefU = as_global(gu.coef.get());
                 S.coefL32 = as_global(gl.coef32.get());
                 S.coefU32 = as_global(gu.coef32.get());
+                S.gpiv = as_global(gu.piv.get());
+                S.gpiv32 = as_global(gu.piv32.get());
             }
             S.chL = as_global(fl.chunk_ptr.get());
             S.rowL = as_global(fl.row.get());

@@ -264,12 +264,23 @@ struct hec_grid {
     int64_t sa = 0, sb = 0, sc = 0;
     hec::DevBuf<double> coef;  // [claim][step][k][lane]; k = 3 (upper): the reciprocal pivot
     hec::DevBuf<float> coef32;
+    hec::DevBuf<double> piv;  // upper, if the batched solver takes it: the pivots [claim][step][lane]
+    hec::DevBuf<float> piv32;
     // 3D: two faces of 8 values for each step of the kernel; 2D: one value a step
     int64_t face_elems() const {
         return (int64_t)PA * PB * (TA == hec::plan::kGT ? (S + 3 * hec::plan::kGridLag + 7) / 8 * 8 * 16 : S);
     }
     int64_t pad_elems() const { return (int64_t)PA * PB * S * 64; }  // positions (claim, step, lane)
 };
+
+namespace hec {
+// Whether the batched solver takes a system's triangles by their wavefront plans: its
+// wavefronts hold one tile each, on a 3D grid up to two.
+constexpr int kBatchWaves = 8;
+inline bool batch_takes_grid(const hec_grid &g) {
+    return g.on && (int64_t)g.PA * g.PB <= (g.TA == plan::kGT ? 2 : 1) * kBatchWaves;
+}
+}  // namespace hec
 
 struct hec_tri {
     int32_t nlev = 0;
@@ -370,6 +381,9 @@ void level_only(const hec_ilu_s &M, bool upper, hec_tri &tri);
 // Builds the level schedule and blocked solve plan of one triangle of M (the
 // upper plan must be built first: the lower plan records positions in it).
 void build_tri(const hec_ilu_s &M, bool upper, hec_tri &tri, const hec_tri *upper_plan, hipStream_t s);
+
+// Packs the pivots of the upper wavefront plan, by which the batched solver divides.
+void build_grid_pivots(const hec_ilu_s &M, hec_grid &upper, hipStream_t s);
 
 // Builds tri.flat (level-ordered copy for the batched solver) for one triangle of M.
 void build_flat(const hec_ilu_s &M, bool upper, hec_tri &tri, hipStream_t s);

@@ -614,6 +614,7 @@ hec_status level_schedule(hec_ilu M, void *stream, hec_levels *out) {
         if (!lv->ras && M->n <= HEC_BATCH_MAX_N) {  // small enough for the batched solver
             build_flat(*M, false, lv->lower, s);
             build_flat(*M, true, lv->upper, s);
+            if (batch_takes_grid(lv->upper.grid)) build_grid_pivots(*M, lv->upper.grid, s);
         }
         lv->sync.alloc(kLevelsSyncWords);
         HEC_HIP(hipMemsetAsync(lv->sync.get(), 0, kLevelsSyncWords * sizeof(uint32_t), s));

@@ -1673,6 +1673,20 @@ __global__ __launch_bounds__(256) void k_grid_coef(int64_t total, int upper, int
     }
 }
 
+// The pivots of an upper wavefront plan, one thread per step and lane (1 where it has no row).
+template <class T>
+__global__ __launch_bounds__(256) void k_grid_piv(int64_t total, int32_t NA, int32_t NB, int32_t NC, int32_t PA,
+                                                  int32_t PB, int TA, int32_t S, int64_t sa, int64_t sb, int64_t sc,
+                                                  const int32_t *__restrict__ diag, const double *__restrict__ LUx,
+                                                  T *__restrict__ out) {
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= total) return;
+    const int64_t claim = (q >> 6) / S;
+    const plan::GridCell g =
+        plan::grid_cell(NA, NB, NC, PA, PB, TA, true, claim, (int)(q & 63), (int32_t)((q >> 6) - claim * S));
+    out[q] = g.valid ? (T)LUx[diag[g.ga * sa + g.gb * sb + g.gc * sc]] : (T)1;
+}
+
 // Before a single-triangle solve: the output filled with the sentinel.
 template <class T>
 __global__ __launch_bounds__(256) void k_trsv_fill(int64_t n, T *x, const int32_t *skip) {
@@ -1937,6 +1951,18 @@ void build_grid(const hec_ilu_s &M, hec_grid &lower, hec_grid &upper, hipStream_
         if (M.has_f32) pack(g.coef32);
         g.on = true;
     }
+}
+
+void build_grid_pivots(const hec_ilu_s &M, hec_grid &g, hipStream_t s) {
+    const int64_t total = g.pad_elems();
+    auto pack = [&](auto &buf) {
+        buf.alloc((size_t)total);
+        k_grid_piv<<<ceil_div(total, 256), 256, 0, s>>>(total, g.NA, g.NB, g.NC, g.PA, g.PB, g.TA, g.S, g.sa, g.sb,
+                                                        g.sc, M.diag.get(), M.LUx.get(), buf.get());
+        HEC_CHECK_LAUNCH();
+    };
+    pack(g.piv);
+    if (M.has_f32) pack(g.piv32);
 }
 
 template void trsv_launch<double>(const hec_levels_s &, uint32_t, const double *, double *, hipStream_t,
