@@ -810,6 +810,13 @@ constexpr size_t grid_lds_bytes() {
     return kGridCtrl + ((size_t)kGridRing * (kGridSlot<UPPER> + kGridRow) + kGridRow) * sizeof(T);
 }
 
+// LDS accesses of one wavefront complete in order: only the compiler is held, so that a value
+// stored before is what another lane of the wavefront reads after.
+__device__ __forceinline__ void lds_order() {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+}
+
 // v of the lane K before in the same 16 lanes; lanes without one: `first`.
 template <int K, class T>
 __device__ __forceinline__ T row_shift(T first, T v) {
@@ -1036,6 +1043,7 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_trsv_grid(GridArgs G, const
                         v *= cur.c1[u].y;
                     }
                     (r0 + u * RS)[8 + lane] = v;
+                    lds_order();  // other lanes read v from there in the next step
                     acc[u] = xp = v;
                 }
                 // an arithmetic result is never the signalling-NaN sentinel (IEEE mode quiets
