@@ -229,9 +229,11 @@ hec_status levels_destroy(hec_levels lv);
  * HEC_ERR_TIMEOUT, and levels_check for trsv_levels. A correct schedule used on
  * one stream at a time never gets there (a wait lasts at most one solve); the
  * limit exists so that a broken plan, a lost store or misuse ends in a status
- * instead of a hung device, and so that tests can force that path. polls < 0
- * restores the default (2^26); 0 gives up at the first unready poll. Applies to
- * launches made after the call, from any thread. */
+ * instead of a hung device, and so that tests can force that path. The waits of
+ * ilu_factor's rows have the same limit; a factorization in which one gives up is
+ * done again with a launch per level, which waits for nothing, so that its caller
+ * sees neither. polls < 0 restores the default (2^26); 0 gives up at the first
+ * unready poll. Applies to launches made after the call, from any thread. */
 hec_status hec_set_spin_limit(int64_t polls);
 
 /* Chooses the triangular-solve kernel of the schedules level_schedule builds after

@@ -74,7 +74,7 @@ static void symbolic_iluk(int32_t n, const int32_t *Ap, const int32_t *Aj, int32
 // produces, so an entry of row p is polled until it is final (device-coherent accesses).
 // Workgroups claim items (rows q0 .. q0 + cnt - 1 of perm, the level order) from a ticket
 // counter, the next claim on its way meanwhile: an item only waits for items of earlier
-// levels, claimed before it by running workgroups.
+// levels, claimed before it by running workgroups. Every wait is bounded (spin_limit).
 //
 // Bound: the chain of levels, each a store and a load between compute units and one
 // division and update per pivot. With a launch per level and one thread per row, its
@@ -82,7 +82,6 @@ static void symbolic_iluk(int32_t n, const int32_t *Ap, const int32_t *Aj, int32
 // with ILU(1) rows and 9.5 ms with rows of up to 512 entries (60,000-row power-law
 // matrix: 285 ms); now 0.56, 2.8 (75 x 62 x 51 ILU(1), 15.4 ms before) and 1.5 ms in all.
 // The values are the same bit for bit.
-constexpr uint32_t kIluSpin = 1u << 26;  // polls of a wait before the factorisation gives up
 constexpr unsigned long long kIluSent = 0x7FF4DEADBEEF1234ull;
 constexpr int kIluCap16 = 96, kIluCap64 = 512;  // longest rows of the two widths (LDS per row)
 
@@ -94,6 +93,7 @@ struct IluArgs {
     double *out;
     int32_t *zero_pivot;
     uint32_t *sync, *err;  // ticket; set when a wait gave up
+    uint32_t spin;         // polls of a wait before it gives up
 };
 
 template <int G>
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
     };
     auto gave_up = [&](uint32_t &it) {  // one more poll of a wait (wave-uniform)
         ++it;
-        if (it > kIluSpin) return true;
+        if (it > A.spin) return true;
         if ((it & 63) == 0 && __hip_atomic_load(A.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return true;
         __builtin_amdgcn_s_sleep(1);
         return false;
@@ -251,8 +251,8 @@ __global__ __launch_bounds__(256) void k_ilu_fill(size_t n, double *__restrict__
     if (i < n) ((unsigned long long *)out)[i] = kIluSent;
 }
 
-// Rows longer than k_ilu_rows keeps in LDS: the rows of one level of L a launch, one
-// thread per row, in place; all rows p were finished by earlier launches.
+// Rows longer than k_ilu_rows keeps in LDS, and where one of its waits gave up: the rows of one
+// level of L a launch, one thread per row, in place; all rows p were finished by earlier launches.
 __global__ __launch_bounds__(256) void k_ilu_level(int32_t cnt, const int32_t *__restrict__ rows,
                                                    const int32_t *__restrict__ LUp,
                                                    const int32_t *__restrict__ LUj,
@@ -298,8 +298,70 @@ __global__ __launch_bounds__(256) void k_convert(size_t n, const S *__restrict__
 
 using namespace hec;
 
+// The numeric phase in one launch (k_ilu_rows): M's values from x0, its entries' start values.
+// zero_pivot: 0, or one past a row whose pivot is zero. false: M's values are not formed (rows
+// too long, or a wait gave up).
+static bool numeric_rows(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &zero_pivot, hipStream_t s) {
+    const int32_t n = M.n;
+    const std::vector<int32_t> &lptr = M.hlptr;
+    int32_t maxlen = 0;
+    for (int32_t i = 0; i < n; ++i) maxlen = std::max(maxlen, M.hLUp[i + 1] - M.hLUp[i]);
+    if (maxlen > kIluCap64) return false;
+    enum : int { FLAG = 0, TICKET = 1, ERR = 2, NFLAGS = 4 };  // zero pivot (row + 1), claims, given up
+    const bool narrow = maxlen <= kIluCap16;
+    const int32_t per = narrow ? 4 : 1;  // rows of a wavefront: 16 or 64 lanes each
+    std::vector<int32_t> items;
+    items.reserve(2 * ((size_t)n / per + nlev));
+    for (int32_t l = 0; l < nlev; ++l)
+        for (int32_t q = lptr[l]; q < lptr[l + 1]; q += per) {
+            items.push_back(q);
+            items.push_back(std::min(per, lptr[l + 1] - q));
+        }
+    const int32_t nitems = (int32_t)(items.size() / 2);
+    if (nitems == 0) return true;
+    DevBuf<int32_t> dperm(n), dflag(NFLAGS), ditems(items.size());
+    DevBuf<double> din(M.nnz);
+    dperm.upload(M.hlperm.data(), n, s);
+    ditems.upload(items.data(), items.size(), s);
+    din.upload(x0, M.nnz, s);
+    HEC_HIP(hipMemsetAsync(dflag.get(), 0, NFLAGS * sizeof(int32_t), s));
+    k_ilu_fill<<<ceil_div(M.nnz, 256), 256, 0, s>>>(M.nnz, M.LUx.get());
+    HEC_CHECK_LAUNCH();
+    const IluArgs args{nitems,       (const int2 *)ditems.get(), dperm.get(),  M.LUp.get(), M.LUj.get(),
+                       M.diag.get(), din.get(),                  M.LUx.get(), dflag.get() + FLAG,
+                       (uint32_t *)dflag.get() + TICKET, (uint32_t *)dflag.get() + ERR, spin_limit()};
+    const unsigned grid = std::min(ceil_div(nitems, 4), 1024u);
+    if (narrow)
+        k_ilu_rows<16><<<grid, 256, ilu_lds_bytes<16>(), s>>>(args);
+    else
+        k_ilu_rows<64><<<grid, 256, ilu_lds_bytes<64>(), s>>>(args);
+    HEC_CHECK_LAUNCH();
+    int32_t hflag[NFLAGS] = {};
+    dflag.download(hflag, NFLAGS, s);
+    HEC_HIP(hipStreamSynchronize(s));
+    zero_pivot = hflag[FLAG];
+    return hflag[ERR] == 0;
+}
+
+// The same with a launch per level (k_ilu_level), which waits for nothing: what numeric_rows
+// could not form.
+static void numeric_levels(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &zero_pivot, hipStream_t s) {
+    DevBuf<int32_t> dperm(M.n), dflag(1);
+    dperm.upload(M.hlperm.data(), M.n, s);
+    HEC_HIP(hipMemsetAsync(dflag.get(), 0, sizeof(int32_t), s));
+    M.LUx.upload(x0, M.nnz, s);
+    for (int32_t l = 1; l < nlev; ++l) {  // level 0 rows have no L entries: nothing to do
+        const int32_t a = M.hlptr[l], cnt = M.hlptr[l + 1] - a;
+        k_ilu_level<<<ceil_div(cnt, 256), 256, 0, s>>>(cnt, dperm.get() + a, M.LUp.get(), M.LUj.get(), M.diag.get(),
+                                                       M.LUx.get(), dflag.get());
+        HEC_CHECK_LAUNCH();
+    }
+    dflag.download(&zero_pivot, 1, s);
+    HEC_HIP(hipStreamSynchronize(s));
+}
+
 // ILU(k) of a CSR matrix (validated, every diagonal stored): host symbolic phase
-// (Eq. (9)-(10)), device numeric phase level by level (Alg. 2 restricted to S_k).
+// (Eq. (9)-(10)), device numeric phase (Alg. 2 restricted to S_k).
 static std::unique_ptr<hec_ilu_s> factor_csr(int32_t n, const int32_t *Ap, const int32_t *Aj, const double *Ax,
                                             int32_t k, uint32_t flags, hipStream_t s) {
     auto M = std::make_unique<hec_ilu_s>();
@@ -331,62 +393,16 @@ static std::unique_ptr<hec_ilu_s> factor_csr(int32_t n, const int32_t *Ap, const
     M->LUj.upload(M->hLUj.data(), M->nnz, s);
     M->diag.upload(M->hdiag.data(), n, s);
     // numeric elimination in level order of L
-    std::vector<int32_t> &lptr = M->hlptr, &perm = M->hlperm, items;
-    int32_t nlev = plan::compute_levels(n, M->hLUp.data(), M->hLUj.data(), M->hdiag.data(), false, lptr, perm);
-    int32_t maxlen = 0;
-    for (int32_t i = 0; i < n; ++i) maxlen = std::max(maxlen, M->hLUp[i + 1] - M->hLUp[i]);
-    enum : int { FLAG = 0, TICKET = 1, ERR = 2, NFLAGS = 4 };  // zero pivot (row + 1), claims, given up
-    DevBuf<int32_t> dperm(n), dflag(NFLAGS), ditems;
-    DevBuf<double> din;
-    dperm.upload(perm.data(), n, s);
-    HEC_HIP(hipMemsetAsync(dflag.get(), 0, NFLAGS * sizeof(int32_t), s));
-    if (maxlen <= kIluCap64) {
-        const bool narrow = maxlen <= kIluCap16;
-        const int32_t per = narrow ? 4 : 1;  // rows of a wavefront: 16 or 64 lanes each
-        items.reserve(2 * ((size_t)n / per + nlev));
-        for (int32_t l = 0; l < nlev; ++l)
-            for (int32_t q = lptr[l]; q < lptr[l + 1]; q += per) {
-                items.push_back(q);
-                items.push_back(std::min(per, lptr[l + 1] - q));
-            }
-        ditems.alloc(items.size());
-        ditems.upload(items.data(), items.size(), s);
-        din.alloc(M->nnz);
-        din.upload(x0, M->nnz, s);
-        if (M->nnz) {
-            k_ilu_fill<<<ceil_div(M->nnz, 256), 256, 0, s>>>(M->nnz, M->LUx.get());
-            HEC_CHECK_LAUNCH();
-        }
-        const int32_t nitems = (int32_t)(items.size() / 2);
-        const IluArgs args{nitems,          (const int2 *)ditems.get(), dperm.get(), M->LUp.get(), M->LUj.get(),
-                           M->diag.get(),   din.get(),                  M->LUx.get(), dflag.get() + FLAG,
-                           (uint32_t *)dflag.get() + TICKET, (uint32_t *)dflag.get() + ERR};
-        const unsigned grid = std::min(ceil_div(nitems, 4), 1024u);
-        if (nitems) {
-            if (narrow)
-                k_ilu_rows<16><<<grid, 256, ilu_lds_bytes<16>(), s>>>(args);
-            else
-                k_ilu_rows<64><<<grid, 256, ilu_lds_bytes<64>(), s>>>(args);
-            HEC_CHECK_LAUNCH();
-        }
-    } else {
-        M->LUx.upload(x0, M->nnz, s);
-        for (int32_t l = 1; l < nlev; ++l) {  // level 0 rows have no L entries: nothing to do
-            int32_t a = lptr[l], cnt = lptr[l + 1] - lptr[l];
-            k_ilu_level<<<ceil_div(cnt, 256), 256, 0, s>>>(cnt, dperm.get() + a, M->LUp.get(), M->LUj.get(),
-                                                           M->diag.get(), M->LUx.get(), dflag.get());
-            HEC_CHECK_LAUNCH();
-        }
-    }
-    int32_t hflag[NFLAGS] = {};
-    dflag.download(hflag, NFLAGS, s);
-    HEC_HIP(hipStreamSynchronize(s));
-    if (hflag[ERR]) fail(HEC_ERR_TIMEOUT, "a wait of the ILU factorisation gave up");
-    int32_t zp = hflag[FLAG];
+    const int32_t nlev =
+        plan::compute_levels(n, M->hLUp.data(), M->hLUj.data(), M->hdiag.data(), false, M->hlptr, M->hlperm);
+    int32_t zp = 0;
+    if (!numeric_rows(*M, nlev, x0, zp, s)) numeric_levels(*M, nlev, x0, zp, s);
     if (zp) fail(HEC_ERR_ZERO_PIVOT, "zero pivot in row " + std::to_string(zp - 1));
     // every pivot u_ii must be nonzero for the backward substitution, also
     // those of rows that no later row uses
     if (n) {
+        DevBuf<int32_t> dflag(1);
+        HEC_HIP(hipMemsetAsync(dflag.get(), 0, sizeof(int32_t), s));
         k_check_diag<<<ceil_div(n, 256), 256, 0, s>>>(n, M->diag.get(), M->LUx.get(), dflag.get());
         HEC_CHECK_LAUNCH();
         dflag.download(&zp, 1, s);
