@@ -251,8 +251,9 @@ __global__ __launch_bounds__(256) void k_ilu_fill(size_t n, double *__restrict__
     if (i < n) ((unsigned long long *)out)[i] = kIluSent;
 }
 
-// Rows longer than k_ilu_rows keeps in LDS, and where one of its waits gave up: the rows of one
-// level of L a launch, one thread per row, in place; all rows p were finished by earlier launches.
+// Rows longer than k_ilu_rows keeps in LDS, and where one of its waits gave up or its start
+// values find no memory: the rows of one level of L a launch, one thread per row, in place;
+// all rows p were finished by earlier launches.
 __global__ __launch_bounds__(256) void k_ilu_level(int32_t cnt, const int32_t *__restrict__ rows,
                                                    const int32_t *__restrict__ LUp,
                                                    const int32_t *__restrict__ LUj,
@@ -300,7 +301,7 @@ using namespace hec;
 
 // The numeric phase in one launch (k_ilu_rows): M's values from x0, its entries' start values.
 // zero_pivot: 0, or one past a row whose pivot is zero. false: M's values are not formed (rows
-// too long, or a wait gave up).
+// too long, a wait gave up, or no memory for the start values beside the factor's).
 static bool numeric_rows(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &zero_pivot, hipStream_t s) {
     const int32_t n = M.n;
     const std::vector<int32_t> &lptr = M.hlptr;
@@ -319,8 +320,18 @@ static bool numeric_rows(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &
         }
     const int32_t nitems = (int32_t)(items.size() / 2);
     if (nitems == 0) return true;
-    DevBuf<int32_t> dperm(n), dflag(NFLAGS), ditems(items.size());
-    DevBuf<double> din(M.nnz);
+    DevBuf<int32_t> dperm, dflag, ditems;
+    DevBuf<double> din;
+    try {
+        dperm.alloc(n);
+        dflag.alloc(NFLAGS);
+        ditems.alloc(items.size());
+        din.alloc(M.nnz);
+    } catch (const Error &e) {
+        if (e.code != HEC_ERR_NOMEM) throw;
+        (void)hipGetLastError();  // not for the next launch's check
+        return false;
+    }
     dperm.upload(M.hlperm.data(), n, s);
     ditems.upload(items.data(), items.size(), s);
     din.upload(x0, M.nnz, s);
@@ -343,8 +354,8 @@ static bool numeric_rows(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &
     return hflag[ERR] == 0;
 }
 
-// The same with a launch per level (k_ilu_level), which waits for nothing: what numeric_rows
-// could not form.
+// The same with a launch per level (k_ilu_level), which waits for nothing and works in place:
+// what numeric_rows could not form.
 static void numeric_levels(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &zero_pivot, hipStream_t s) {
     DevBuf<int32_t> dperm(M.n), dflag(1);
     dperm.upload(M.hlperm.data(), M.n, s);

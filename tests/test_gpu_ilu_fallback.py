@@ -1,7 +1,8 @@
 """ilu_factor's rows wait on the device for the rows they eliminate with, each wait bounded by
 hec_set_spin_limit. Where one gives up, forced here with a limit of zero polls, the factorisation is done
-again with a launch per level, which waits for nothing: the caller gets the same values bit for bit, no
-status of its own, and all temporary memory back."""
+again with a launch per level, which waits for nothing, and so it is where there is no memory for the start
+values beside the factor (that way works in place): the caller gets the same values bit for bit, no status
+of its own, and all temporary memory back."""
 import numpy as np
 import pytest
 
@@ -41,3 +42,35 @@ def test_zero_spin_limit_leaves_the_factor_as_it_is(name, counting):  # noqa: F8
     assert calls1 == calls
     for g in (got, again):
         assert all(np.array_equal(a, b) for a, b in zip(g, want))
+
+
+class Budget(Counting):
+    """Refuses what would take the live bytes over a limit."""
+    limit = None
+
+    def alloc(self, nbytes, stream):
+        return 0 if self.limit is not None and self.bytes + nbytes > self.limit else super().alloc(nbytes, stream)
+
+
+@pytest.mark.parametrize("name", MATRICES)
+def test_an_allocator_that_holds_the_factor_alone_serves_it(name):
+    """No more memory than the factor, a row order and a flag word: the values are formed in place."""
+    make, k = MATRICES[name]
+    A = make()
+    c = Budget()
+    hec.set_allocator(c.alloc, c.free)
+    try:
+        (LUp, LUj, LUx), _ = _factor(A, k, c)
+        n, nnz = A.n, LUx.size
+        need = 4 * (n + 1) + 4 * nnz + 4 * n + 8 * nnz + 4 * n + 4
+        c.limit = need
+        F = hec.ilu_factor(A, k=k)
+        out = hec.ilu_export(F)
+        F.close()
+        assert all(np.array_equal(a, b) for a, b in zip(out, (LUp, LUj, LUx)))
+        c.limit = need - 4 * n - 4  # the factor fits, the row order does not
+        with pytest.raises(hec.HecError) as e:
+            hec.ilu_factor(A, k=k)
+        assert e.value.code == hec.NOMEM and c.bytes == 0
+    finally:
+        hec.use_torch_allocator()
