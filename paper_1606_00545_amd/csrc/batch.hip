@@ -844,7 +844,9 @@ hec_status gmres_solve_batched(hec_batch B, int32_t count, const hec_matrix *A, 
             if (a->n > 0 && (!b[i] || !x[i])) fail(HEC_ERR_INVALID_ARG, "b or x is NULL");
             if (mixed && (!a->has_f32 || !f->has_f32))
                 fail(HEC_ERR_INVALID_ARG, "mixed precision needs HEC_KEEP_F32 on the matrix and the factor");
-            if (a->n > 0 && (l->lower.flat.nchunks == 0 || l->upper.flat.nchunks == 0))
+            const hec_grid &gl = l->lower.grid, &gu = l->upper.grid;
+            const bool by_grid = gl.on && batch_takes_grid(gu) && gu.piv.get();
+            if (a->n > 0 && !by_grid && (l->lower.flat.nchunks == 0 || l->upper.flat.nchunks == 0))
                 fail(HEC_ERR_INVALID_ARG, "levels handle has no level-ordered copy (n above HEC_BATCH_MAX_N)");
             BatchSys &S = B->h_sys[i];
             S.n = a->n;
@@ -864,9 +866,8 @@ hec_status gmres_solve_batched(hec_batch B, int32_t count, const hec_matrix *A, 
             S.ldq = fl.ldq;
             S.nchL = fl.nchunks;
             S.nchU = fu.nchunks;
-            const hec_grid &gl = l->lower.grid, &gu = l->upper.grid;
             S.ntiles = 0;
-            if (gl.on && batch_takes_grid(gu)) {
+            if (by_grid) {
                 S.ntiles = gl.PA * gl.PB;
                 S.TA = gl.TA;
                 S.NA = gl.NA;

@@ -285,7 +285,8 @@ inline bool batch_takes_grid(const hec_grid &g) {
 struct hec_tri {
     int32_t nlev = 0;
     std::vector<int32_t> hlevel_ptr, hperm;  // Alg. 3: level start pointers, rows by (level, row)
-    hec_flat flat;                           // small systems only: level-ordered copy for the batched solver
+    hec_flat flat;                           // level-ordered copy for the batched solver: small systems that it
+                                             // does not take by their wavefront plans
     int32_t K = 0, KC = 4, ldq = 0, nparts = 0, nss = 0, W = 0, S = 0;  // KC: K padded to 4/8/16/32
     int32_t NS = 1;                          // solver wavefronts per workgroup
     int32_t D64 = 0, D32 = 0;                // ring depths for the FP64 / FP32 solve
@@ -339,9 +340,9 @@ struct hec_levels_s {
     bool ras = false;
     hec_tri lower, upper;
     hec::DevBuf<uint32_t> sync;  // part tickets + finished-workgroup counters
-    // Internal vectors over the factor's rows. qL/qU: each triangle's results in its own
-    // plan's position order, the copy dependent rows poll (qL is sentinel-filled between
-    // solves; qU is filled by every lower launch, or before a lone upper solve). yp:
+    // Internal vectors over the factor's rows. qL/qU (not with wavefront plans): each
+    // triangle's results in its own plan's position order, the copy dependent rows poll
+    // (qL is sentinel-filled between solves; qU is filled by every lower launch, or before a lone upper solve). yp:
     // L^{-1} b in the upper plan's order, the upper solve's right-hand side (with the
     // wavefront plans: by claim, step and lane of the lower plan, padded).
     hec::DevBuf<double> qL64, qU64, yp64;

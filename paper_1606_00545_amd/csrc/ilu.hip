@@ -639,22 +639,26 @@ hec_status level_schedule(hec_ilu M, void *stream, hec_levels *out) {
             build_tri(*M, false, lv->lower, &lv->upper, s);
         }
         if (!lv->ras && M->n <= HEC_BATCH_MAX_N) {  // small enough for the batched solver
-            build_flat(*M, false, lv->lower, s);
-            build_flat(*M, true, lv->upper, s);
-            if (batch_takes_grid(lv->upper.grid)) build_grid_pivots(*M, lv->upper.grid, s);
+            if (batch_takes_grid(lv->upper.grid)) {
+                build_grid_pivots(*M, lv->upper.grid, s);
+            } else {
+                build_flat(*M, false, lv->lower, s);
+                build_flat(*M, true, lv->upper, s);
+            }
         }
         lv->sync.alloc(kLevelsSyncWords);
         HEC_HIP(hipMemsetAsync(lv->sync.get(), 0, kLevelsSyncWords * sizeof(uint32_t), s));
-        lv->qL64.alloc(M->n);
-        lv->qU64.alloc(M->n);
         const int64_t ny = lv->lower.grid.on ? std::max<int64_t>(M->n, lv->lower.grid.pad_elems()) : M->n;
         lv->yp64.alloc(ny);
-        if (M->has_f32) {
-            lv->qL32.alloc(M->n);
-            lv->qU32.alloc(M->n);
-            lv->yp32.alloc(ny);
-        }
-        if (lv->lower.grid.on) {
+        if (M->has_f32) lv->yp32.alloc(ny);
+        if (!lv->lower.grid.on) {
+            lv->qL64.alloc(M->n);
+            lv->qU64.alloc(M->n);
+            if (M->has_f32) {
+                lv->qL32.alloc(M->n);
+                lv->qU32.alloc(M->n);
+            }
+        } else {
             const int64_t nface = lv->lower.grid.face_elems();
             lv->fL64.alloc(nface);
             lv->fU64.alloc(nface);
@@ -723,7 +727,7 @@ hec_status trsv_levels(hec_ilu M, hec_levels lv, uint32_t which, hec_dtype prec,
         if (prec == HEC_F64) {
             trsv_launch<double>(*lv, which, (const double *)b, (double *)x, s);
         } else if (prec == HEC_F32) {
-            if (!M->has_f32 || (!lv->qL32.get() && lv->n > 0))
+            if (!M->has_f32 || (!lv->yp32.get() && lv->n > 0))
                 fail(HEC_ERR_INVALID_ARG, "factor has no FP32 copy (HEC_KEEP_F32)");
             trsv_launch<float>(*lv, which, (const float *)b, (float *)x, s);
         } else {

@@ -1891,8 +1891,10 @@ void trsv_launch(const hec_levels_s &lv, uint32_t which, const T *b, T *x, hipSt
 void trsv_init_levels(hec_levels_s &lv, hipStream_t s) {
     const int64_t n = lv.nf;
     if (n == 0) return;
-    k_trsv_fill<double><<<ceil_div(n, 256), 256, 0, s>>>(n, lv.qL64.get(), nullptr);
-    HEC_CHECK_LAUNCH();
+    if (lv.qL64.get()) {
+        k_trsv_fill<double><<<ceil_div(n, 256), 256, 0, s>>>(n, lv.qL64.get(), nullptr);
+        HEC_CHECK_LAUNCH();
+    }
     if (lv.qL32.get()) {
         k_trsv_fill<float><<<ceil_div(n, 256), 256, 0, s>>>(n, lv.qL32.get(), nullptr);
         HEC_CHECK_LAUNCH();
