@@ -28,7 +28,7 @@ static void symbolic_iluk(int32_t n, const int32_t *Ap, const int32_t *Aj, int32
         LUj.assign(Aj, Aj + Ap[n]);
         for (int32_t i = 0; i <= n; ++i) LUp[i] = Ap[i];
         for (int32_t i = 0; i < n; ++i)
-            for (int32_t e = Ap[i]; e < Ap[i + 1]; ++e)
+            for (int32_t e = Ap[i]; e < Ap[i + 1] && diag[i] < 0; ++e)
                 if (Aj[e] == i) diag[i] = e;
         return;
     }
@@ -66,52 +66,66 @@ static void symbolic_iluk(int32_t n, const int32_t *Ap, const int32_t *Aj, int32
 
 // ------------------------------------------------------------------ numeric ILU kernel
 
-// Numeric elimination (Alg. 2 restricted to S_k) in one launch. G lanes take a row i,
-// 64 / G rows of one level of L a wavefront: for each stored p < i in ascending order,
-// l_ip = a_ip / u_pp, then a_ij -= l_ip * u_pj for every stored (p, j), j > p, that is
-// also in row i, the lanes taking the entries of row p. Row i is worked on in LDS and
-// written to `out` once; `out` starts filled with a signalling NaN that arithmetic never
-// produces, so an entry of row p is polled until it is final (device-coherent accesses).
-// Workgroups claim items (rows q0 .. q0 + cnt - 1 of perm, the level order) from a ticket
-// counter, the next claim on its way meanwhile: an item only waits for items of earlier
-// levels, claimed before it by running workgroups. Every wait is bounded (spin_limit).
+// Numeric elimination (Alg. 2 restricted to S_k) in one launch. Some lanes take a row i: for
+// each stored p < i in ascending order, l_ip = a_ip / u_pp, then a_ij -= l_ip * u_pj for every
+// stored (p, j), j > p, that is also in row i, the lanes taking the entries of row p. A row is
+// worked on apart (in LDS, or where it is too long for that in its entries of `in`) and written
+// to `out` once; `out` starts filled with a signalling NaN that arithmetic never produces, so an
+// entry of row p is polled until it is final (device-coherent accesses).
+// Workgroups claim four items from a ticket counter, a wavefront each, the next claim on its
+// way meanwhile: an item, rows of one level of L, only waits for items of earlier levels,
+// claimed before it by running workgroups. Every wait is bounded (spin_limit).
+//
+// An item is up to four rows of at most kIluShort entries, 16 lanes each, or one longer row
+// with the whole wavefront: chosen row by row, so that a long row costs the others nothing.
+// Four rows of kIluShort (7.5 KB) and one of kIluLds (10 KB) take a wavefront about the same LDS:
+// 40 KB a workgroup, three of them on a compute unit. Rows beyond kIluLds look their columns up
+// and keep their values in memory. With kIluLds = 97, 256, 512 and 1,024 a 60,000-row power-law
+// matrix (rows of 4 to 512) takes 1.71, 1.63, 1.38 and 1.78 ms, 20,000 rows of 4 to 2,000 2.31,
+// 2.19, 2.24 and 2.78 (514 with a launch per level).
 //
 // Bound: the chain of levels, each a store and a load between compute units and one
 // division and update per pivot. With a launch per level and one thread per row, its
 // loads one after another, a level took 15 us (60^3 ILU(0), 178 levels: 2.7 ms), 45 us
 // with ILU(1) rows and 9.5 ms with rows of up to 512 entries (60,000-row power-law
-// matrix: 285 ms); now 0.56, 2.8 (75 x 62 x 51 ILU(1), 15.4 ms before) and 1.5 ms in all.
+// matrix: 285 ms); now 0.57, 2.7 (75 x 62 x 51 ILU(1), 15.4 ms before) and 1.38 ms in all.
 // The values are the same bit for bit.
 constexpr unsigned long long kIluSent = 0x7FF4DEADBEEF1234ull;
-constexpr int kIluCap16 = 96, kIluCap64 = 512;  // longest rows of the two widths (LDS per row)
+constexpr int kIluShort = 96;  // most entries of a row that shares a wavefront with three others
+constexpr int kIluLds = 512;   // most entries of a row worked on in LDS
+constexpr int kIluGroup = 4;   // rows of a short item
 
 struct IluArgs {
     int32_t nitems;
-    const int2 *items;
+    const int2 *items;  // (first row in perm, rows; 0 rows: one row of more than kIluShort entries)
     const int32_t *perm, *LUp, *LUj, *diag;
-    const double *in;
+    double *in;  // start values; a row beyond kIluLds entries is worked on there
     double *out;
     int32_t *zero_pivot;
     uint32_t *sync, *err;  // ticket; set when a wait gave up
     uint32_t spin;         // polls of a wait before it gives up
 };
 
-template <int G>
+// LDS of a wavefront's rows: per entry its value, its column and, if it is a pivot's, the
+// pivot's diagonal and the end of its row.
+template <bool LONG>
+constexpr int ilu_wave_entries() {
+    return LONG && kIluLds > kIluGroup * kIluShort ? kIluLds : kIluGroup * kIluShort;
+}
+template <bool LONG>
 constexpr size_t ilu_lds_bytes() {
-    return (size_t)4 * (64 / G) * (G == 16 ? kIluCap16 : kIluCap64) * (sizeof(double) + 3 * sizeof(int32_t));
+    return (size_t)4 * ilu_wave_entries<LONG>() * (sizeof(double) + 3 * sizeof(int32_t));
 }
 
-template <int G>
+// LONG: there are rows of more than kIluShort entries.
+template <bool LONG>
 __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
     using U = unsigned long long;
-    constexpr int CAP = G == 16 ? kIluCap16 : kIluCap64;
     extern __shared__ __align__(16) char ism[];
     __shared__ int s_claim[2], s_abort[2];  // by the round's parity
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane % G, grp = threadIdx.x / G;
-    double *const vals = (double *)ism + grp * CAP;  // the group's row: values, columns, and per
-    int32_t *const cols = (int32_t *)((double *)ism + 4 * (64 / G) * CAP) + grp * 3 * CAP;
-    int32_t *const pdiag = cols + CAP, *const pend = cols + 2 * CAP;  // pivot: its diagonal, its row's end
+    double *const wvals = (double *)ism + wave * ilu_wave_entries<LONG>();
+    int32_t *const wints = (int32_t *)((double *)ism + 4 * ilu_wave_entries<LONG>()) + wave * 3 * ilu_wave_entries<LONG>();
     auto poll = [&](const double *p) {
         return __hip_atomic_load((const U *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
@@ -122,31 +136,44 @@ __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
         __builtin_amdgcn_s_sleep(1);
         return false;
     };
-    auto lds_order = [] {  // LDS accesses of one wavefront complete in order: only the compiler is held
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_wave_barrier();
-    };
     struct Piv {  // pivot row p: this lane's entry u of its upper part, its place in row i, and u_pp
         int32_t u, pe, f;
         U v, d;
         const double *pv, *pd;
     };
     constexpr int NP = 4;  // pivots whose entries are waited for together
-    // false: a wait gave up
-    auto factor = [&](int32_t q0, int32_t cnt) {
-        const bool live = lane / G < cnt;
-        const int32_t i = A.perm[q0 + (live ? lane / G : 0)];
+    // Rows q0 .. q0 + cnt - 1 of perm, G lanes each, in LDS (at most CAP entries) or in `in`
+    // (CAP = 0); false: a wait gave up.
+    auto factor = [&](auto gc, auto cc, int32_t q0, int32_t cnt) {
+        constexpr int G = decltype(gc)::value, CAP = decltype(cc)::value;
+        const int g = lane % G, grp = lane / G;
+        const bool live = grp < cnt;
+        const int32_t i = A.perm[q0 + (live ? grp : 0)];
         const int32_t b0 = A.LUp[i], len = live ? A.LUp[i + 1] - b0 : 0, nl = live ? A.diag[i] - b0 : 0;
-        for (int e = g; e < len; e += G) {
-            const int32_t c = A.LUj[b0 + e];
-            cols[e] = c;
-            vals[e] = A.in[b0 + e];
-            if (e < nl) {
-                pdiag[e] = A.diag[c];
-                pend[e] = A.LUp[c + 1];
+        double *const vals = CAP ? wvals + grp * CAP : A.in + b0;
+        int32_t *const lcols = wints + grp * 3 * CAP, *const pdiag = lcols + CAP, *const pend = pdiag + CAP;
+        const int32_t *const cols = CAP ? lcols : A.LUj + b0;
+        auto order = [] {  // what the row's lanes stored is what they read after
+            if constexpr (CAP != 0)  // (LDS accesses of a wavefront complete in order: only the compiler is held)
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            else
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+        };
+        if constexpr (CAP != 0) {
+            for (int e = g; e < len; e += G) {
+                const int32_t c = A.LUj[b0 + e];
+                lcols[e] = c;
+                vals[e] = A.in[b0 + e];
+                if (e < nl) {
+                    pdiag[e] = A.diag[c];
+                    pend[e] = A.LUp[c + 1];
+                }
             }
         }
-        lds_order();
+        order();
+        auto diag_of = [&](int e) { return CAP ? pdiag[e] : A.diag[cols[e]]; };   // of pivot e, in LUx
+        auto end_of = [&](int e) { return CAP ? pend[e] : A.LUp[cols[e] + 1]; };  // of pivot e's row
         auto place = [&](int e, int32_t j) -> int32_t {  // of column j in row i past entry e, -1: not stored
             int lo = e + 1, hi = len;
             while (lo < hi) {
@@ -172,17 +199,18 @@ __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
                 const bool in = e0 + k < nl;
-                P[k].pe = in ? pend[e0 + k] : 0;
-                P[k].pd = P[k].pv = A.out + (in ? pdiag[e0 + k] : 0);
+                const int32_t pd = in ? diag_of(e0 + k) : 0;
+                P[k].pe = in ? end_of(e0 + k) : 0;
+                P[k].pd = P[k].pv = A.out + pd;
                 P[k].d = in ? poll(P[k].pd) : 0;
-                load(e0 + k, in ? pdiag[e0 + k] + 1 + g : 0, in, P[k]);
+                load(e0 + k, in ? pd + 1 + g : 0, in, P[k]);
             }
             uint32_t it = 0;
             for (;;) {  // until the entries of all NP pivots are final; only the pending ones are loaded again
-                bool pend = false;
+                bool pending = false;
 #pragma unroll
-                for (int k = 0; k < NP; ++k) pend |= P[k].v == kIluSent || P[k].d == kIluSent;
-                if (__ballot(pend) == 0) break;
+                for (int k = 0; k < NP; ++k) pending |= P[k].v == kIluSent || P[k].d == kIluSent;
+                if (__ballot(pending) == 0) break;
                 if (gave_up(it)) return false;
 #pragma unroll
                 for (int k = 0; k < NP; ++k) {
@@ -200,7 +228,7 @@ __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
                 }
                 const bool act = e < nl && !stop;
                 const double lip = act ? vals[e] / upp : 0.0;
-                lds_order();
+                order();
                 if (act && g == 0) vals[e] = lip;
                 if (act && P[k].f >= 0) vals[P[k].f] -= lip * __longlong_as_double((long long)P[k].v);
                 // entries of row p past the first G
@@ -213,7 +241,7 @@ __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
                     }
                     if (act && P[k].f >= 0) vals[P[k].f] -= lip * __longlong_as_double((long long)P[k].v);
                 }
-                lds_order();
+                order();
             }
         }
         for (int e = g; e < len; e += G) {
@@ -221,8 +249,21 @@ __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
             if (v == kIluSent) v = 0x7FF8000000000000ull;  // an input that is the sentinel: a quiet NaN
             __hip_atomic_store((U *)(A.out + b0 + e), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        lds_order();
+        order();
         return true;
+    };
+    auto item_rows = [&](int2 item) {
+        const int32_t q0 = __builtin_amdgcn_readfirstlane(item.x), cnt = __builtin_amdgcn_readfirstlane(item.y);
+        if constexpr (LONG) {
+            if (cnt == 0) {
+                const int32_t i = A.perm[q0];
+                const int32_t len = __builtin_amdgcn_readfirstlane(A.LUp[i + 1] - A.LUp[i]);
+                if (len <= kIluLds)
+                    return factor(std::integral_constant<int, 64>(), std::integral_constant<int, kIluLds>(), q0, 1);
+                return factor(std::integral_constant<int, 64>(), std::integral_constant<int, 0>(), q0, 1);
+            }
+        }
+        return factor(std::integral_constant<int, 64 / kIluGroup>(), std::integral_constant<int, kIluShort>(), q0, cnt);
     };
     if (threadIdx.x == 0) {
         s_abort[0] = s_abort[1] = 0;
@@ -235,12 +276,9 @@ __global__ __launch_bounds__(256) void k_ilu_rows(IluArgs A) {
         uint32_t next = 0;
         if (threadIdx.x == 0) next = atomicAdd(A.sync, 1u);
         const int t = c * 4 + wave;
-        if (t < A.nitems) {
-            const int2 item = A.items[t];
-            if (!factor(__builtin_amdgcn_readfirstlane(item.x), __builtin_amdgcn_readfirstlane(item.y))) {
-                __hip_atomic_store(A.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_abort[(round + 1) & 1] = 1;
-            }
+        if (t < A.nitems && !item_rows(A.items[t])) {
+            __hip_atomic_store(A.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_abort[(round + 1) & 1] = 1;
         }
         if (threadIdx.x == 0) s_claim[(round + 1) & 1] = (int)next;
     }
@@ -251,9 +289,8 @@ __global__ __launch_bounds__(256) void k_ilu_fill(size_t n, double *__restrict__
     if (i < n) ((unsigned long long *)out)[i] = kIluSent;
 }
 
-// Rows longer than k_ilu_rows keeps in LDS, and where one of its waits gave up or its start
-// values find no memory: the rows of one level of L a launch, one thread per row, in place;
-// all rows p were finished by earlier launches.
+// Where a wait of k_ilu_rows gave up or its start values find no memory: the rows of one level
+// of L a launch, one thread per row, in place; all rows p were finished by earlier launches.
 __global__ __launch_bounds__(256) void k_ilu_level(int32_t cnt, const int32_t *__restrict__ rows,
                                                    const int32_t *__restrict__ LUp,
                                                    const int32_t *__restrict__ LUj,
@@ -300,24 +337,30 @@ __global__ __launch_bounds__(256) void k_convert(size_t n, const S *__restrict__
 using namespace hec;
 
 // The numeric phase in one launch (k_ilu_rows): M's values from x0, its entries' start values.
-// zero_pivot: 0, or one past a row whose pivot is zero. false: M's values are not formed (rows
-// too long, a wait gave up, or no memory for the start values beside the factor's).
+// zero_pivot: 0, or one past a row whose pivot is zero. false: M's values are not formed (a wait
+// gave up, or no memory for the start values beside the factor's).
 static bool numeric_rows(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &zero_pivot, hipStream_t s) {
     const int32_t n = M.n;
-    const std::vector<int32_t> &lptr = M.hlptr;
-    int32_t maxlen = 0;
-    for (int32_t i = 0; i < n; ++i) maxlen = std::max(maxlen, M.hLUp[i + 1] - M.hLUp[i]);
-    if (maxlen > kIluCap64) return false;
     enum : int { FLAG = 0, TICKET = 1, ERR = 2, NFLAGS = 4 };  // zero pivot (row + 1), claims, given up
-    const bool narrow = maxlen <= kIluCap16;
-    const int32_t per = narrow ? 4 : 1;  // rows of a wavefront: 16 or 64 lanes each
-    std::vector<int32_t> items;
-    items.reserve(2 * ((size_t)n / per + nlev));
-    for (int32_t l = 0; l < nlev; ++l)
-        for (int32_t q = lptr[l]; q < lptr[l + 1]; q += per) {
-            items.push_back(q);
-            items.push_back(std::min(per, lptr[l + 1] - q));
+    auto is_long = [&](int32_t i) { return M.hLUp[i + 1] - M.hLUp[i] > kIluShort; };
+    bool any_long = false;
+    for (int32_t i = 0; i < n && !any_long; ++i) any_long = is_long(i);
+    std::vector<int32_t> perm, items;  // perm: inside each level the long rows, which take longest, first
+    items.reserve(2 * ((size_t)n / kIluGroup + nlev));
+    if (any_long) perm = M.hlperm;
+    for (int32_t l = 0; l < nlev; ++l) {
+        const int32_t b = M.hlptr[l + 1];
+        int32_t q = M.hlptr[l];
+        if (any_long) {
+            const int32_t a = q;
+            q = (int32_t)(std::stable_partition(perm.begin() + a, perm.begin() + b, is_long) - perm.begin());
+            for (int32_t t = a; t < q; ++t) items.insert(items.end(), {t, 0});
         }
+        for (; q < b; q += kIluGroup) {
+            items.push_back(q);
+            items.push_back(std::min(kIluGroup, b - q));
+        }
+    }
     const int32_t nitems = (int32_t)(items.size() / 2);
     if (nitems == 0) return true;
     DevBuf<int32_t> dperm, dflag, ditems;
@@ -332,7 +375,7 @@ static bool numeric_rows(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &
         (void)hipGetLastError();  // not for the next launch's check
         return false;
     }
-    dperm.upload(M.hlperm.data(), n, s);
+    dperm.upload(any_long ? perm.data() : M.hlperm.data(), n, s);
     ditems.upload(items.data(), items.size(), s);
     din.upload(x0, M.nnz, s);
     HEC_HIP(hipMemsetAsync(dflag.get(), 0, NFLAGS * sizeof(int32_t), s));
@@ -342,10 +385,10 @@ static bool numeric_rows(hec_ilu_s &M, int32_t nlev, const double *x0, int32_t &
                        M.diag.get(), din.get(),                  M.LUx.get(), dflag.get() + FLAG,
                        (uint32_t *)dflag.get() + TICKET, (uint32_t *)dflag.get() + ERR, spin_limit()};
     const unsigned grid = std::min(ceil_div(nitems, 4), 1024u);
-    if (narrow)
-        k_ilu_rows<16><<<grid, 256, ilu_lds_bytes<16>(), s>>>(args);
+    if (any_long)
+        k_ilu_rows<true><<<grid, 256, ilu_lds_bytes<true>(), s>>>(args);
     else
-        k_ilu_rows<64><<<grid, 256, ilu_lds_bytes<64>(), s>>>(args);
+        k_ilu_rows<false><<<grid, 256, ilu_lds_bytes<false>(), s>>>(args);
     HEC_CHECK_LAUNCH();
     int32_t hflag[NFLAGS] = {};
     dflag.download(hflag, NFLAGS, s);
