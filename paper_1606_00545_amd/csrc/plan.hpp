@@ -322,11 +322,12 @@ inline int32_t choose_tile_side(int32_t n, const std::vector<int32_t> &lev, int3
 //    NS > 1 also wide enough that the results of a sub-segment never replace
 //    an entry that a sub-segment which may still run reads.
 //  * D64/D32: LDS ring depth for the FP64/FP32 solves; 0 when the plan does not
-//    fit in LDS (more than 32 entries per row): then blocked == false and the
-//    solve polls every dependency (level-order positions in 64-row chunks).
-//    flat == true asks for that level-order layout directly. long_slab == false
-//    leaves enc, src and psrc of a plan that does not fit to make_row_plan (a slab as
-//    wide as the longest row is mostly padding there).
+//    fit in LDS (more than 32 entries per row): then blocked == false, positions
+//    are in level order and chunks cuts each level into 64 rows. flat == true asks
+//    for that layout directly (the batched solver walks its chunks). The solve of a
+//    plan that does not fit polls every dependency row by row: it is laid out by
+//    make_row_plan, and long_slab == false leaves enc, src and psrc to that (a slab
+//    as wide as the longest row is mostly padding there).
 struct HostPlan {
     int32_t n = 0, nlev = 0, K = 0, KC = 4, ldq = 0, nparts = 0, nss = 0, W = 64, S = 0, D64 = 0, D32 = 0, NS = 1;
     bool blocked = false;
@@ -575,6 +576,10 @@ inline void make_plan(int32_t n, const int32_t *LUp, const int32_t *LUj, const i
         if (upper) P.psrc[q] = diag[i];
     }
 }
+
+constexpr int kRowShort = 64;  // most entries of a row solved by a group of 8 lanes: one
+                               // or two batches of 4 per lane; longer rows take a wavefront
+constexpr int kRowGroup = 8;   // rows of a short item
 
 // Row layout of a plan that is not blocked (made with long_slab == false): inside each
 // level the rows of more than `shortmax` entries come first, then the others, both by

@@ -76,6 +76,60 @@ int64_t hecplan_array(const void *h, const char *name, int32_t *dst) {
 
 void hecplan_free(void *h) { delete (HostPlan *)h; }
 
+// Row layout (make_row_plan) of the strict lower (upper) triangle, with the bounds the
+// library uses, for a plan that does not fit in LDS; NULL if it does fit, or on allocation
+// failure. blocks as for hecplan_make.
+struct RowPlan {
+    HostPlan P;
+    std::vector<int32_t> rptr, items;
+};
+
+void *hecplan_rows_make(int32_t n, const int32_t *LUp, const int32_t *LUj, const int32_t *diag, int32_t upper,
+                        int64_t lds_max, const int32_t *blocks, int32_t nbounds) {
+    auto *R = new (std::nothrow) RowPlan();
+    if (!R) return nullptr;
+    try {
+        std::vector<int32_t> bv;
+        if (blocks && nbounds > 0) bv.assign(blocks, blocks + nbounds);
+        hec::plan::make_plan(n, LUp, LUj, diag, 0, 0, 0, upper != 0, true, lds_max, R->P, false,
+                             bv.empty() ? nullptr : &bv, hec::plan::kSolvers, 0, false);
+        if (!R->P.blocked) {
+            hec::plan::make_row_plan(n, LUp, LUj, diag, upper != 0, hec::plan::kRowShort, hec::plan::kRowGroup, R->P,
+                                     R->rptr, R->items);
+            return R;
+        }
+    } catch (...) {
+    }
+    delete R;
+    return nullptr;
+}
+
+// Copies the named array (rptr, items, enc, src, grow, pos, psrc, lev) into dst when dst !=
+// NULL. Returns its length, or -1 for an unknown name.
+int64_t hecplan_rows_array(const void *h, const char *name, int32_t *dst) {
+    const RowPlan &R = *(const RowPlan *)h;
+    const std::vector<int32_t> *v = nullptr;
+    if (!std::strcmp(name, "rptr")) v = &R.rptr;
+    else if (!std::strcmp(name, "items")) v = &R.items;
+    else if (!std::strcmp(name, "enc")) v = &R.P.enc;
+    else if (!std::strcmp(name, "src")) v = &R.P.src;
+    else if (!std::strcmp(name, "grow")) v = &R.P.grow;
+    else if (!std::strcmp(name, "pos")) v = &R.P.pos;
+    else if (!std::strcmp(name, "psrc")) v = &R.P.psrc;
+    else if (!std::strcmp(name, "lev")) v = &R.P.lev;
+    if (!v) return -1;
+    if (dst && !v->empty()) std::memcpy(dst, v->data(), v->size() * sizeof(int32_t));
+    return (int64_t)v->size();
+}
+
+// out = {kRowShort, kRowGroup}.
+void hecplan_rows_bounds(int32_t *out) {
+    out[0] = hec::plan::kRowShort;
+    out[1] = hec::plan::kRowGroup;
+}
+
+void hecplan_rows_free(void *h) { delete (RowPlan *)h; }
+
 // Wavefront plan of the strict lower (upper) triangle on the nx x ny x nz grid
 // (make_grid_plan); NULL when none applies or on allocation failure.
 void *hecplan_grid_make(int32_t n, const int32_t *LUp, const int32_t *LUj, const int32_t *diag, int32_t gnx,

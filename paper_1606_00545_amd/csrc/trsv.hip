@@ -609,9 +609,8 @@ __global__ __launch_bounds__(kBlkThreads) void k_trsv_blk(PlanArgs P, const T *_
 // (every row walking the longest row's slots, one batch of polls after another) took
 // 5.78 ms for the L-then-U pair of a 60,000-row power-law ILU(0) (rows of 4 to 512
 // entries, 31 levels); this takes 0.15 ms.
-constexpr int kRowShort = 64;  // most entries of a row solved by a group of 8 lanes: one
-                               // or two batches of 4 per lane; longer rows take a wavefront
-constexpr int kRowGroup = 8;   // rows of a short item
+using plan::kRowGroup;
+using plan::kRowShort;
 constexpr int kRowWaves = 8;   // wavefronts per workgroup, one item each per claim
 
 template <class T, bool UPPER>
