@@ -163,7 +163,10 @@ hec_status hec_destroy(hec_matrix A);
  * a_ip /= a_pp; a_ij -= a_ip a_pj for (i,j) in S_k) runs on the device, rows
  * grouped by the Eq. (11) levels of L. L (unit diagonal implied) and U share one
  * array, as in the paper. Every row must store its diagonal (INVALID_ARG
- * otherwise); an exactly zero pivot gives ZERO_PIVOT. flags: HEC_KEEP_F32. */
+ * otherwise); an exactly zero pivot gives ZERO_PIVOT. While it runs it takes 8
+ * bytes for each entry of the factor and up to 12 for each row beside it; where
+ * these are refused it runs in place, slower, with 4 for each row. flags:
+ * HEC_KEEP_F32. */
 hec_status ilu_factor(int32_t n, const int32_t *Ap, const int32_t *Aj, const double *Ax, int32_t k,
                       uint32_t flags, void *stream, hec_ilu *out);
 
@@ -244,10 +247,10 @@ hec_status hec_set_spin_limit(int64_t polls);
  * gets wavefront plans for both triangles: tiles of 8 x 8 grid columns (3D) or
  * 64 x 1 (2D, at least 16 columns across), one wavefront each, whose lanes step
  * through the levels together, passing results between neighbouring lanes. Every
- * other factor, and every factor with enable = 0, gets the level-blocked plans. A schedule keeps the kind it was
- * built with (levels_grid reports it). Both kernels perform each row's
- * subtractions (fused multiply-adds) and may differ in rounding only where their
- * order differs. INVALID_ARG unless enable is 0 or 1. */
+ * other factor, and every factor with enable = 0, gets the level-blocked plans. A
+ * schedule keeps the kind it was built with (levels_grid reports it). Both kernels
+ * perform each row's subtractions (fused multiply-adds) and may differ in rounding
+ * only where their order differs. INVALID_ARG unless enable is 0 or 1. */
 hec_status hec_set_trsv_grid(int32_t enable);
 
 /* Synchronises `stream`, then reports (and clears) a wait of lv's triangular

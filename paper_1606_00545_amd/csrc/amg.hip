@@ -1,6 +1,6 @@
 // Algebraic multigrid (Sec. 2.8, Alg. 5): host setup (Ruge-Stueben coarsening,
 // direct interpolation, Galerkin coarse operators) and a device V-cycle with
-// damped Jacobi smoothing built on the HEC SpMV.
+// damped Jacobi or Chebyshev smoothing, each step of it one launch.
 //
 // Setup, per level (plain C++ on the host; the same steps, in the same order of
 // operations, as a reference implementation can follow by hand):
@@ -21,7 +21,7 @@
 //    column order, (A_c)_IJ over the fine rows i in ascending order;
 // until a level has at most coarse_size rows, max_levels levels exist, or no
 // coarsening happens. The coarsest level is solved exactly with its inverse
-// (Gauss-Jordan with partial pivoting on the host), applied as a dense SpMV.
+// (Gauss-Jordan with partial pivoting on the host), applied as a dense product.
 //
 // Solve: x = 0, then V-cycles (Alg. 5) until ||b - A x|| <= rtol ||b||: nu1
 // damped Jacobi sweeps x += omega D^{-1} (b - A x), the residual restricted with

@@ -94,7 +94,7 @@ struct BatchSys {
 };
 
 struct BatchHead {
-    int32_t count, restart, maxit, precision, x0_zero;
+    int32_t count, restart, maxit, x0_zero;
     uint32_t spin;  // polls a wait for a dependency makes before it gives up
     double rtol, target, inner_rtol;
 };
@@ -454,7 +454,9 @@ __device__ __forceinline__ void b_grid_tri(const BatchSys &S, const BatchSys *sy
     }
 }
 
-// out = U^{-1} L^{-1} v (Eq. (7)-(8)), also left in LDS; returns where. Ends with a barrier.
+// out = U^{-1} L^{-1} v (Eq. (7)-(8)), also left in LDS, where it is whole on return; returns
+// where. No barrier follows the stores to out on the grid path: every thread may read its own
+// rows of it (i, i + kBT, ..), for others' it needs one.
 template <class VT>
 __device__ __forceinline__ const double *b_prec(const BatchSys &S, const BatchSys *sys, const GDouble *v, GDouble *out, const Lds &L,
                                                 uint32_t spin, int *timed_out) {
@@ -906,7 +908,6 @@ hec_status gmres_solve_batched(hec_batch B, int32_t count, const hec_matrix *A, 
         Hh.count = count;
         Hh.restart = B->restart;
         Hh.maxit = o->maxit;
-        Hh.precision = o->precision;
         Hh.x0_zero = o->x0_zero;
         Hh.spin = spin_limit();
         Hh.rtol = o->rtol;

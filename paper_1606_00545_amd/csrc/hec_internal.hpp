@@ -262,7 +262,9 @@ struct hec_grid {
     int32_t TA = 8;  // tile side along a: 8 (8 x 8 tiles, 3D grid) or 64 (64 x 1, 2D grid)
     int32_t NA = 0, NB = 0, NC = 0, PA = 0, PB = 0, S = 0;
     int64_t sa = 0, sb = 0, sc = 0;
-    hec::DevBuf<double> coef;  // [claim][step][k][lane]; k = 3 (upper): the reciprocal pivot
+    // 3D: [claim][step][k][lane], k = back, below, left and (upper) the reciprocal pivot; 2D: per
+    // claim and step 64 pairs (back, left), then (upper) 64 reciprocal pivots
+    hec::DevBuf<double> coef;
     hec::DevBuf<float> coef32;
     hec::DevBuf<double> piv;  // upper, if the batched solver takes it: the pivots [claim][step][lane]
     hec::DevBuf<float> piv32;
