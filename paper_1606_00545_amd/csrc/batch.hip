@@ -301,7 +301,7 @@ template <> __device__ __forceinline__ const GFloat *gpiv<float>(const HEC_CONST
 // took 142 us and a 16^3 system's 59; now 33 and 29. A row of U is divided by its pivot in FP64,
 // as in level order (FP32 pivots too): a product with the packed reciprocal, in FP32 an FP32
 // number, has up to 2^-24 more error a row; 48 systems of 1,000 to 4,200 rows took 5.3 ms
-// with it and take 5.7. The quotient from a reciprocal of its own and one correction by the
+// with it and take 5.7 to 5.9. The quotient from a reciprocal of its own and one correction by the
 // remainder, with the guards that makes it the same for every operand: 6.0 ms.
 // Not inlined: with its registers allocated apart from the solver's, the levels ahead stay
 // in registers (a spill reload in the loop waits for every load in flight).
