@@ -203,8 +203,9 @@ def use_torch_allocator():
 
 
 def set_spin_limit(polls: int = -1):
-    """hec_set_spin_limit: polls a device-side wait of the triangular solves makes before
-    it gives up (negative: the default)."""
+    """hec_set_spin_limit: polls a device-side wait of the triangular solves, or of a
+    factorization (which is then done again without waits), makes before it gives up
+    (negative: the default)."""
     _check(load().hec_set_spin_limit(int(polls)), "hec_set_spin_limit")
 
 
